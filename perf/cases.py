@@ -1,0 +1,262 @@
+"""Timed calls of the restore path: what an engine asks of this library.
+
+A case is a plain dict:
+
+  op       "restore": one request, probe -> bind -> every window -> commit -> end
+           "pair":    two requests of their own prompts bound together under a
+                      staging budget of two rings, their windows interleaved
+           "probe":   the lookup alone (every admitted prompt pays it, hit or not)
+           "store":   one prompt's chunks put into the pinned-host store
+  layout   allocator groups, see LAYOUTS
+  chunk    tokens per chunk
+  tokens   prompt length; a ragged tail past the last full chunk is never stored
+  held     share of the prompt's full chunks that the store holds (a prefix)
+  window   W, 0 = whole-plan mode
+  order    "packed": the prompt's chunks were stored with one call, back to back
+           "scattered": one call each, in a random order, as chunks of several
+           prompts arrive at a store that serves them all
+  trusted  block tables checked on the device instead of read back at bind
+
+The file tier is left out: its rate is that of the host's disk or page cache.
+"""
+
+from __future__ import annotations
+
+import numpy as np
+import torch
+
+from paper_2608_17826_amd import bsr
+from paper_2608_17826_amd.session import RestoreSession, group_dsts
+
+VOCAB = 129_280
+C, P = bsr.BSR_KIND_CONTIG, bsr.BSR_KIND_PLANAR
+
+# (block_tokens, n_tensors, record_bytes, kind, split_bytes) per group
+LAYOUTS = {
+    # two MLA latent tensors (576 bf16 values per token): the 1K-token workload
+    "one": [(16, 2, 1152, C, 0)],
+    # MLA latent and index keys (128 fp8 values and an fp32 scale): 32K to 512K workloads
+    "two": [(64, 32, 1152, C, 0), (128, 8, 132, P, 128)],
+    # 170 tensors in four groups: the 512K workload with sliding-window and MTP groups
+    "mtp": [(64, 30, 1152, C, 0), (128, 116, 132, P, 128), (32, 21, 512, C, 0), (64, 3, 1152, C, 0)],
+    # eight groups whose blocks divide the chunk, exceed it, or neither, with
+    # records that are no multiples of 16 bytes
+    "eight": [(8, 2, 64, C, 0), (16, 1, 36, P, 32), (64, 3, 20, C, 0), (24, 2, 132, P, 128),
+              (32, 1, 1152, C, 0), (5, 2, 12, C, 0), (48, 1, 24, P, 8), (128, 2, 512, C, 0)],
+}
+CHUNKS = {"one": (64, 256), "two": (16, 64, 100, 256), "mtp": (64, 256), "eight": (32,)}
+LARGEST_BYTES = 3_200_000_000  # payload of the largest listed case, rounded up
+
+
+def listed():
+    def restore(name, layout, chunk, tokens, window, order="packed", held=1.0, trusted=False, op="restore"):
+        return {"name": name, "op": op, "layout": layout, "chunk": chunk, "tokens": tokens, "held": held,
+                "window": window, "order": order, "trusted": trusted}
+    return [
+        # the smallest request: a short system prompt of a small model, W = 2
+        restore("tiny-1k", "one", 64, 1024, 2),
+        # a short turn over eight ragged groups
+        restore("eight-groups-1k", "eight", 32, 1287, 32),
+        # a chat prompt of a few thousand tokens, 64-token chunks, stored as they came
+        restore("chat-2k", "two", 64, 2000, 8, order="scattered"),
+        # the same engine with chunks of one 16-token block
+        restore("chat-4k-chunk16", "two", 16, 4111, 32),
+        # a document prompt, four groups, half the usual window
+        restore("doc-8k-mtp", "mtp", 256, 8192, 16, trusted=True),
+        # a document prompt restored from a store that has served others, small window
+        restore("doc-16k-scattered", "two", 256, 16_400, 8, order="scattered"),
+        # the 32K workload
+        restore("prompt-32k", "two", 256, 32_768, 32),
+        # a long context of the four-group layout, three quarters of it held
+        restore("long-64k-mtp", "mtp", 256, 65_536, 32, held=0.75),
+        # two prompts restored side by side under an admission budget
+        restore("pair-8k", "two", 256, 8192, 8, op="pair"),
+        # lookup of a long prompt, three quarters of it held
+        restore("probe-128k", "one", 256, 131_072, 32, held=0.75, op="probe"),
+        # retention of a prompt that was just computed
+        restore("store-4k", "two", 256, 4096, 32, op="store"),
+    ]
+
+
+def draw(rng):
+    op = rng.choice(["restore"] * 8 + ["pair", "probe", "store"])
+    layout = rng.choice(["one", "two", "two", "mtp", "eight"])
+    if op == "store" and layout == "eight":
+        layout = "two"
+    chunk = rng.choice(CHUNKS[layout])
+    per_token = sum(nt * rb for _, nt, rb, _, _ in LAYOUTS[layout])
+    most = {"restore": LARGEST_BYTES, "pair": LARGEST_BYTES // 4, "probe": LARGEST_BYTES // 4,
+            "store": 15 * chunk * per_token}[op] // per_token
+    most = min(most, 131_072)
+    least = min(most, max(2 * chunk, 500))
+    tokens = int(round(least * (most / least) ** rng.random()))
+    window = rng.choice([2, 8, 8, 16, 32, 32, 64] + ([0] if op == "restore" else []))
+    return {"op": op, "layout": layout, "chunk": chunk, "tokens": tokens, "held": rng.choice([1.0, 1.0, 0.75, 0.4]),
+            "window": window, "order": rng.choice(["packed", "scattered"]), "trusted": rng.choice([False, False, True])}
+
+
+def _chunks(case):
+    """(full chunks, held chunks) of the prompt; at least one is held."""
+    full = case["tokens"] // case["chunk"]
+    return full, max(1, int(full * case["held"]))
+
+
+def _payload(case):
+    return sum(nt * rb for _, nt, rb, _, _ in LAYOUTS[case["layout"]]) * case["chunk"]
+
+
+def work(case):
+    full, held = _chunks(case)
+    look = case["tokens"] * 4 + full * 8  # tokens read, keys written
+    moved = 2 * held * _payload(case)     # each chunk read once and written once
+    return {"bytes": {"restore": look + moved, "pair": 2 * (look + moved), "probe": look, "store": moved}[case["op"]],
+            "flops": 0}
+
+
+def tolerance(case):
+    return "exact"  # bytes are moved, keys and tags are whole numbers
+
+
+class _State:
+    """A context, its store, and what one caller keeps with it."""
+
+    def __init__(self, ctx):
+        self.ctx = ctx
+        self.reqs = []
+
+    def __del__(self):
+        self.reqs = []
+        bsr.bsr_ctx_destroy(self.ctx)
+
+
+class _Request:
+    """A prompt, its destination pools and its session."""
+
+
+def _records(n, record_bytes, split, gen):
+    """uint8 [n, record_bytes]: bf16 N(0, 1) values, or fp8 values and their fp32 scale."""
+    if record_bytes == split + 4 and split >= 128:
+        x = torch.randn(n, split, generator=gen, device="cuda")
+        scale = x.abs().amax(1, keepdim=True) / 448.0
+        q = (x / scale).to(torch.float8_e4m3fn).view(torch.uint8)
+        return torch.cat([q, scale.view(torch.uint8)], 1).cpu().numpy()
+    x = torch.randn(n, record_bytes // 2, generator=gen, device="cuda").to(torch.bfloat16)
+    return x.view(torch.uint8).cpu().numpy()
+
+
+def prepare(case, seed):
+    groups, chunk = LAYOUTS[case["layout"]], case["chunk"]
+    rng = np.random.default_rng(seed)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    layout = bsr.make_layout(chunk, groups)
+    W, n_req = case["window"], 2 if case["op"] == "pair" else 1
+    full, held = _chunks(case)
+    slot = bsr.bsr_slot_bytes(layout)
+    budget = 2 * W * slot if n_req == 2 else 0
+    s = _State(bsr.bsr_ctx_create(layout, W, hip_device=0, flags=bsr.BSR_FLAG_TRUSTED_TABLES if case["trusted"] else 0,
+                                  staging_budget_bytes=budget, max_bound_requests=2 if budget else 0))
+    s.op = case["op"]
+    stride = (slot + 4095) // 4096 * 4096
+    if s.op == "store":  # the caller's own pinned arena, with room for a prompt and its replacement
+        s.arena = torch.empty(stride * (2 * held + 1), dtype=torch.uint8, pin_memory=True)
+        bsr.bsr_store_adopt(s.ctx, s.arena.data_ptr(), s.arena.numel())
+    else:
+        bsr.bsr_store_reserve(s.ctx, stride * (held * n_req + 1))
+
+    # every entry is a window of a seeded base of its group, at an offset of its own
+    bases = [_records(nt * chunk + held * n_req, rb, sp, gen) for _, nt, rb, _, sp in groups]
+    offs = [rng.permutation(held * n_req) for _ in groups]
+
+    def entry(i):
+        return [b[o[i]:o[i] + nt * chunk].reshape(-1) for b, o, (_, nt, _, _, _) in zip(bases, offs, groups)]
+
+    jobs = []
+    for r in range(n_req):
+        q = _Request()
+        q.rid = 1 + r
+        q.tokens = rng.integers(0, VOCAB, size=case["tokens"], dtype=np.int32)
+        q.salt = int(rng.integers(1, 1 << 62))
+        q.keys = bsr.bsr_chunk_keys(q.salt, q.tokens, chunk)[:held]
+        jobs += [(int(k), r * held + i) for i, k in enumerate(q.keys)]
+        s.reqs.append(q)
+    if s.op == "store":
+        s.keys, s.entries, s.n_groups = [k for k, _ in jobs], [entry(i) for _, i in jobs], len(groups)
+        return s
+    if case["order"] == "packed":
+        bsr.bsr_store_put_chunks(s.ctx, [k for k, _ in jobs], [entry(i) for _, i in jobs])
+    else:
+        for j in rng.permutation(len(jobs)):
+            bsr.bsr_store_put_chunk(s.ctx, jobs[j][0], entry(jobs[j][1]))
+    if s.op == "probe":
+        return s
+
+    for q in s.reqs:
+        q.pools, q.bases, q.tables, q.valid, q.pool_blocks = [], [], [], [], []
+        for bt, nt, rb, _, _ in groups:
+            need = -(-full * chunk // bt)
+            pb = -(-2 * need // 4) * 4  # pools twice the request, tensors 16-byte aligned
+            pool = torch.full((nt, pb * bt * rb), 37, dtype=torch.uint8, device="cuda")
+            q.pools.append(pool)
+            q.bases.append(torch.tensor([pool[t].data_ptr() for t in range(nt)], dtype=torch.int64, device="cuda"))
+            q.tables.append(torch.from_numpy(rng.permutation(pb)[:need].astype(np.int32)).cuda())
+            q.valid.append(torch.zeros(pb, dtype=torch.uint8, device="cuda"))
+            q.pool_blocks.append(pb)
+        q.dsts = group_dsts(q.tables, q.bases, q.valid, q.pool_blocks)
+        q.session = RestoreSession(s.ctx)
+    return s
+
+
+def _restored(q, exposed, fallback):
+    return {"exposed": exposed, "fallback": fallback, "valid": q.valid, "pools": [p.view(torch.int32) for p in q.pools]}
+
+
+def _run_restore(s):
+    (q,) = s.reqs
+    n, _, _ = bsr.bsr_probe(s.ctx, q.rid, q.salt, q.tokens)
+    q.session.bind(q.rid, n, q.dsts)
+    for first, cnt in q.session.next_windows(q.rid):
+        bsr.bsr_restore_window(s.ctx, q.rid, first, cnt)
+    exposed, fallback = bsr.bsr_commit(s.ctx, q.rid)
+    bsr.bsr_request_end(s.ctx, q.rid)
+    return _restored(q, exposed, fallback)
+
+
+def _run_pair(s):
+    for q in s.reqs:
+        n, _, _ = bsr.bsr_probe(s.ctx, q.rid, q.salt, q.tokens)
+        q.session.bind(q.rid, n, q.dsts)
+    left = list(s.reqs)
+    while left:  # one window of each request in turn
+        for q in list(left):
+            first, cnt = bsr.bsr_next_window(s.ctx, q.rid)
+            if cnt:
+                bsr.bsr_restore_window(s.ctx, q.rid, first, cnt)
+            else:
+                left.remove(q)
+    out = [_restored(q, *bsr.bsr_commit(s.ctx, q.rid)) for q in s.reqs]
+    for q in s.reqs:
+        bsr.bsr_request_end(s.ctx, q.rid)
+    return out
+
+
+def _run_probe(s):
+    (q,) = s.reqs
+    n, bitmap, keys = bsr.bsr_probe(s.ctx, q.rid, q.salt, q.tokens)
+    bsr.bsr_request_end(s.ctx, q.rid)
+    return {"n": n, "bitmap": bitmap, "keys": keys.view(np.int64)}
+
+
+def _run_store(s):
+    bsr.bsr_store_put_chunks(s.ctx, s.keys, s.entries)
+    stored, tags = [], []
+    for k in s.keys:
+        for g in range(s.n_groups):
+            addr, nbytes, tag = bsr.bsr_store_payload(s.ctx, k, g)
+            tags.append(tag)
+            at = addr - s.arena.data_ptr()
+            stored.append(s.arena[at:at + nbytes].view(torch.int32))
+    return {"stored": stored, "tags": np.asarray(tags, dtype=np.uint64).view(np.int64)}
+
+
+def run(state):
+    return {"restore": _run_restore, "pair": _run_pair, "probe": _run_probe, "store": _run_store}[state.op](state)
