@@ -126,7 +126,8 @@ class _State:
 
     def __del__(self):
         self.reqs = []
-        bsr.bsr_ctx_destroy(self.ctx)
+        if bsr is not None:  # None once the interpreter is shutting down
+            bsr.bsr_ctx_destroy(self.ctx)
 
 
 class _Request:
