@@ -267,34 +267,44 @@ struct FinishParams {
   GroupValid g[BSR_MAX_GROUPS];
 };
 
-// Staging copy (pinned host memory -> ring slot) done by a kernel on the
-// copy stream instead of the copy engine.  src is the device's view of the
-// pinned source, 16-byte aligned; dst is in the ring, 16-byte aligned; bytes
-// is a multiple of 4.  The host checks both ranges before every launch.
-struct StageParams {
+// Staging copy (pinned host memory -> ring slots) done by a kernel on the
+// copy stream instead of the copy engine.  One launch takes a list of runs: a
+// run is a range of pinned memory and the range of the ring it goes to.  src
+// is the device's view of the pinned source and dst is in the ring, both
+// 16-byte aligned; bytes is a positive multiple of 4.  The host checks both
+// ranges of every run before the launch.
+struct StageRun {
   const uint8_t* src;
   uint8_t* dst;
   uint64_t bytes;
 };
+// Runs of one launch: one per chunk of an install batch when no two of its
+// chunks are adjacent in the arena.
+constexpr uint32_t kStageMaxRuns = BSR_MAX_INSTALL_BATCH;
+struct StageParams {
+  uint32_t n_runs;
+  uint32_t n_tiles;                        // of all runs
+  uint32_t first_tile[kStageMaxRuns + 1];  // run i owns tiles [first_tile[i], first_tile[i + 1])
+  StageRun run[kStageMaxRuns];
+};
 // Shape: the host link needs about its bandwidth-delay product in flight,
 // and reads queued beyond it delay the install's HBM traffic when the two
-// overlap.  24 workgroups x 256 threads x 2 vectors keep 192 KiB in flight.
-// Measured on one box, 512K 4-group workload (grid x vectors, KiB in
-// flight: restore GB/s at W = 32, install's share of 8 TB/s at W = 32 and
-// W = 8): 24 x 2, 192: 56.84, 76.5%, 62.9%; 32 x 2, 256: 56.87, 74.3%,
-// 55.8%; 48 x 1, 192: 56.61, 75.1% (W = 32 only); 16 x 2 and 32 x 1, 128:
-// 56.44-56.59, 79.1%, 72.4%; 64 x 4, 1 MiB: installs three times slower.
-// Staging that keeps less in flight moves less over the link (8 x 4, 128:
-// 55.9 GB/s of link), so 192 KiB is the shape that keeps the link's rate.
+// overlap.  24 workgroups x 256 threads with two 16-byte vectors each (one of
+// each of two tiles) keep 192 KiB in flight.  Measured on one box with one
+// vector per tile (grid, KiB in flight: link GB/s in 1 GiB launches; restore
+// GB/s and the install's share of 8 TB/s, 24,576 tokens of the 4-group layout
+// at W = 8): 16, 128: 57.29, 56.1, 73.9%; 24, 192: 57.54, 56.4, 67.3%; 32,
+// 256: 57.59, 56.4, 58.1%; 48, 384: 55.8, 54.9, 38.5%.  Tiles of 8 KiB (two
+// vectors per thread and tile) lose link rate: grid 12, 192 KiB: 56.1; 16,
+// 256: 57.2; 24, 384: 55.5.
 #ifndef BSR_STAGE_GRID
 #define BSR_STAGE_GRID 24
 #endif
-#ifndef BSR_STAGE_UNROLL
-#define BSR_STAGE_UNROLL 2
-#endif
 constexpr int kStageThreads = 256;
-constexpr int kStageUnroll = BSR_STAGE_UNROLL;  // 16-byte vectors in flight per thread
 constexpr int kStageMaxGrid = BSR_STAGE_GRID;   // workgroups
+// A workgroup takes one tile of a run at a time, one 16-byte vector per
+// thread; a run's last tile may be partly filled.
+constexpr uint32_t kStageTileBytes = 16u * kStageThreads;
 
 // Scratch of a context that allocates nothing (bsr_ctx_create_static): one
 // array per GPU in the library's code object, holding one session slot's
@@ -328,7 +338,8 @@ hipError_t launch_scatter(const ScatterParams& p, hipStream_t s);
 hipError_t launch_install(const InstallParams& p, uint32_t n_workgroups, hipStream_t s,
                           hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 hipError_t launch_verify(const VerifyParams& p, hipStream_t s);
-hipError_t launch_stage(const StageParams& p, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
+hipError_t launch_stage(const StageRun* runs, uint32_t n_runs, hipStream_t s, hipEvent_t start = nullptr,
+                        hipEvent_t stop = nullptr);
 hipError_t launch_finish(const FinishParams& p, hipStream_t s);
 
 }  // namespace bsr

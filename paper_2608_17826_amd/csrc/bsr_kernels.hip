@@ -1,9 +1,10 @@
 // gfx950 kernels of the bounded-window restore.
 //
-// stage   : copy a run of staged chunks from pinned host memory into the
+// stage   : copy runs of chunks from pinned host memory into the
 //           W-slot ring (§4 windowed retrieve: the window's objects are
 //           brought into the local restore pool), read over the host link
-//           by a small grid on the copy stream.
+//           by a small grid on the copy stream, all runs of an install batch
+//           in one launch.
 // install : scatter staged chunks from the W-slot ring into every group's
 //           paged blocks (§3 "Install locally"; §4 windowed retrieve, whose
 //           per-window step moves the staged window into the engine's
@@ -42,9 +43,6 @@
 #endif
 #ifndef BSR_NT_LOAD
 #define BSR_NT_LOAD 1   // staged chunks are read once: non-temporal loads
-#endif
-#ifndef BSR_STAGE_NT_STORE
-#define BSR_STAGE_NT_STORE 0  // staging-copy stores: 1 non-temporal, 0 ordinary
 #endif
 
 
@@ -651,42 +649,82 @@ __global__ __launch_bounds__(256) void k_finish(const FinishParams p) {
   }
 }
 
-// Staging copy: pinned host memory (the device's view of it) into a ring
-// slot, read over the host link by a small grid (kStageMaxGrid workgroups,
-// kStageUnroll 16-byte loads in flight per thread before its stores).  The
-// stores are ordinary: the install reads the slot next, and non-temporal
-// stores made overlapping installs slower (16 x 4 at W = 32: 167 against
-// 155 us per launch).  Compared with the copy engine (hipMemcpyAsync), a
-// kernel's completion hands over to the install on the compute stream
-// sooner, which is most of what a small window lost per window.
+// Staging copy: runs of pinned host memory (the device's view of them) into
+// ring slots, read over the host link by a small grid.  The tiles of all runs
+// are dealt to the workgroups as one sequence, so the link stays loaded from
+// one run to the next: only the ends of a launch leave it idle, about 3 us.
+// A workgroup has two tiles in flight and issues a tile's loads before it
+// waits for the one before.  Measured on one box (57.5 GB/s of link in 1 GiB
+// launches, as with one run per launch), 6,144 tokens of the 2-group layout:
+// with 16-token chunks (607 KB, no two adjacent in the arena) at W = 32, one
+// launch per chunk 40.1 GB/s and one per batch 52.6; with 64-token chunks
+// (2.4 MB) at W = 8, 50.6 and 52.8; 256-token chunks (9.7 MB) out of a
+// scattered store at W = 8, 55.0 and 55.8.  Both loads of a pair before both
+// stores: 52.2, 52.6 and 55.8.
+// The stores are ordinary: the install reads the slots next, and
+// non-temporal stores made overlapping installs slower (16 x 4 at W = 32: 167
+// against 155 us per launch).  Compared with the copy engine
+// (hipMemcpyAsync), a kernel's completion hands over to the install on the
+// compute stream sooner, which is most of what a small window lost per
+// window.
+struct StageTile {
+  const uint8_t* src;
+  uint8_t* dst;
+  uint32_t bytes;  // 4..kStageTileBytes, a multiple of 4
+};
+
+// Tiles are visited in ascending order, so `r` only moves forward.
+__device__ __forceinline__ StageTile stage_tile(const StageParams& p, uint32_t tile, uint32_t& r) {
+  while (tile >= p.first_tile[r + 1]) ++r;
+  const uint64_t off = static_cast<uint64_t>(tile - p.first_tile[r]) * kStageTileBytes;
+  const uint64_t left = p.run[r].bytes - off;
+  return StageTile{p.run[r].src + off, p.run[r].dst + off,
+                   static_cast<uint32_t>(left < kStageTileBytes ? left : kStageTileBytes)};
+}
+
+// Loads and stores go through buffer resources of the tile's whole vectors:
+// the hardware drops what lies past them, so no lane takes a branch and the
+// compiler can count the loads and stores still in flight.
+__device__ __forceinline__ i32x4 stage_load(const StageTile& t, uint32_t tid) {
+  return __builtin_amdgcn_raw_buffer_load_b128(piece_rsrc(const_cast<uint8_t*>(t.src), t.bytes & ~15u),
+                                               static_cast<int>(tid * 16u), 0, 0);
+}
+
+__device__ __forceinline__ void stage_store(i32x4 v, const StageTile& t, uint32_t tid) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, piece_rsrc(t.dst, t.bytes & ~15u), static_cast<int>(tid * 16u), 0, 0);
+}
+
 __global__ __launch_bounds__(kStageThreads) void k_stage(const StageParams p) {
-  const u32x4* __restrict__ s4 = reinterpret_cast<const u32x4*>(p.src);
-  u32x4* __restrict__ d4 = reinterpret_cast<u32x4*>(p.dst);
-  const uint64_t nvec = p.bytes >> 4;
-  const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kStageThreads;
-  for (uint64_t base = static_cast<uint64_t>(blockIdx.x) * kStageThreads + threadIdx.x; base < nvec;
-       base += stride * kStageUnroll) {
-    u32x4 v[kStageUnroll];
-#pragma unroll
-    for (int u = 0; u < kStageUnroll; ++u) {
-      const uint64_t i = base + u * stride;
-      if (i < nvec) v[u] = *global_ptr(s4 + i);
-    }
-#pragma unroll
-    for (int u = 0; u < kStageUnroll; ++u) {
-      const uint64_t i = base + u * stride;
-#if BSR_STAGE_NT_STORE
-      if (i < nvec) __builtin_nontemporal_store(v[u], global_ptr(d4 + i));
-#else
-      if (i < nvec) *global_ptr(d4 + i) = v[u];
-#endif
-    }
+  const uint32_t tid = threadIdx.x, grid = gridDim.x;
+  uint32_t tile = blockIdx.x, r = 0;
+  if (tile >= p.n_tiles) return;
+  static_assert(kStageMaxRuns * 4 <= kStageThreads, "four threads per run");
+  if (tile == 0 && (tid >> 2) < p.n_runs) {  // each run's tail of up to three words
+    const StageRun& q = p.run[tid >> 2];
+    const uint64_t at = (q.bytes & ~static_cast<uint64_t>(15)) + (tid & 3u) * 4u;
+    if (at < q.bytes)
+      *global_ptr(reinterpret_cast<uint32_t*>(q.dst + at)) = *global_ptr(reinterpret_cast<const uint32_t*>(q.src + at));
   }
-  // a tail of up to three words
-  const uint64_t w0 = nvec * 4, nw = p.bytes >> 2;
-  if (blockIdx.x == 0 && w0 + threadIdx.x < nw)
-    *global_ptr(reinterpret_cast<uint32_t*>(p.dst) + w0 + threadIdx.x) =
-        *global_ptr(reinterpret_cast<const uint32_t*>(p.src) + w0 + threadIdx.x);
+  StageTile ta = stage_tile(p, tile, r);
+  i32x4 va = stage_load(ta, tid);
+  for (;;) {
+    tile += grid;
+    if (tile >= p.n_tiles) {
+      stage_store(va, ta, tid);
+      return;
+    }
+    const StageTile tb = stage_tile(p, tile, r);
+    const i32x4 vb = stage_load(tb, tid);
+    stage_store(va, ta, tid);
+    tile += grid;
+    if (tile >= p.n_tiles) {
+      stage_store(vb, tb, tid);
+      return;
+    }
+    ta = stage_tile(p, tile, r);
+    va = stage_load(ta, tid);
+    stage_store(vb, tb, tid);
+  }
 }
 
 // Plain scattered block copy (the install's ceiling, see ScatterParams):
@@ -785,12 +823,24 @@ hipError_t launch_install(const InstallParams& p, uint32_t n_workgroups, hipStre
   return hipGetLastError();
 }
 
-hipError_t launch_stage(const StageParams& p, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
-  if (((reinterpret_cast<uintptr_t>(p.src) | reinterpret_cast<uintptr_t>(p.dst)) & 15u) || (p.bytes & 3u))
-    return hipErrorInvalidValue;
-  if (p.bytes == 0) return hipSuccess;
-  const uint64_t per_wg = static_cast<uint64_t>(kStageThreads) * kStageUnroll * 16;
-  const uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(kStageMaxGrid, (p.bytes + per_wg - 1) / per_wg));
+hipError_t launch_stage(const StageRun* runs, uint32_t n_runs, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+  if (n_runs == 0) return hipSuccess;
+  if (n_runs > kStageMaxRuns) return hipErrorInvalidValue;
+  StageParams p{};
+  uint64_t tiles = 0;
+  for (uint32_t i = 0; i < n_runs; ++i) {
+    const StageRun& r = runs[i];
+    if (((reinterpret_cast<uintptr_t>(r.src) | reinterpret_cast<uintptr_t>(r.dst)) & 15u) || (r.bytes & 3u) || r.bytes == 0)
+      return hipErrorInvalidValue;
+    p.run[i] = r;
+    p.first_tile[i] = static_cast<uint32_t>(tiles);
+    tiles += (r.bytes + kStageTileBytes - 1) / kStageTileBytes;
+    if (tiles >= (1ull << 31)) return hipErrorInvalidValue;  // tile + grid stays below 2^32
+  }
+  for (uint32_t i = n_runs; i <= kStageMaxRuns; ++i) p.first_tile[i] = static_cast<uint32_t>(tiles);
+  p.n_runs = n_runs;
+  p.n_tiles = static_cast<uint32_t>(tiles);
+  const uint32_t grid = std::min<uint32_t>(kStageMaxGrid, p.n_tiles);
   if (start && stop)
     hipExtLaunchKernelGGL(k_stage, dim3(grid), dim3(kStageThreads), 0, s, start, stop, 0, p);
   else

@@ -480,27 +480,50 @@ int find_active(bsr_ctx* c, uint64_t request_id, Session** out) {
   return BSR_OK;
 }
 
-// A staging copy of `bytes` from host memory `src` into the ring at `dst`, on
-// the copy stream.  When the source lies in a pinned allocation
-// [base, base + extent) whose device view is `dev`, k_stage reads it over
-// the host link; otherwise (or with BSR_FLAG_SDMA_COPIES) the copy engine
-// copies it.  Both ranges are checked here before any kernel is launched:
-// the source inside its pinned allocation, the destination inside this
-// request's ring.
-hipError_t stage_copy(bsr_ctx* c, Session& s, uint8_t* dst, const uint8_t* src, uint64_t bytes, const uint8_t* base,
-                      const uint8_t* dev, uint64_t extent) {
+// Consecutive chunks staged together: `count` chunks from `first` on, from
+// one range of host memory to one range of the ring.
+struct Run {
+  const uint8_t* src = nullptr;
+  uint8_t* dst = nullptr;
+  uint64_t bytes = 0;
+  uint32_t first = 0, count = 0;
+};
+
+// Staging copies of `n` runs (at most kStageMaxRuns) from host memory into
+// the ring, on the copy stream; *done is the runs enqueued, all n on success.
+// When the sources lie in a pinned allocation [base, base + extent) whose
+// device view is `dev`, one k_stage launch reads them all over the host link;
+// otherwise (or with BSR_FLAG_SDMA_COPIES) the copy engine copies them one by
+// one.  All ranges are checked here before any kernel is launched: the source
+// inside its pinned allocation, the destination inside this request's ring.
+hipError_t stage_copy(bsr_ctx* c, Session& s, const Run* runs, uint32_t n, const uint8_t* base, const uint8_t* dev,
+                      uint64_t extent, uint32_t* done) {
+  *done = 0;
   s.copy_dirty = true;
   // With several requests bound, each staging on a copy stream of its own,
   // their k_stage launches would run side by side on the link; the copy
   // engine queues them instead (3 requests of 512K tokens: 56.9 against
   // 56.6 GB/s in aggregate, the installs beside them at 76% of HBM against 67%).
   const bool shared_link = c->bound.size() > 1 && s.copy != s.compute;
-  if (!c->kernel_copies || shared_link || !dev || !base)
-    return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s.copy);
-  const bool src_in = src >= base && bytes <= extent && static_cast<uint64_t>(src - base) <= extent - bytes;
-  const bool dst_in = dst >= s.staging && bytes <= s.ring_bytes &&
-                      static_cast<uint64_t>(dst - s.staging) <= s.ring_bytes - bytes;
-  if (!src_in || !dst_in) return hipErrorInvalidValue;
+  if (!c->kernel_copies || shared_link || !dev || !base) {
+    for (; *done < n; ++*done) {
+      const Run& r = runs[*done];
+      if (hipError_t e = hipMemcpyAsync(r.dst, r.src, r.bytes, hipMemcpyHostToDevice, s.copy)) return e;
+    }
+    return hipSuccess;
+  }
+  bsr::StageRun list[bsr::kStageMaxRuns];
+  uint64_t bytes = 0;
+  if (n > bsr::kStageMaxRuns) return hipErrorInvalidValue;
+  for (uint32_t i = 0; i < n; ++i) {
+    const Run& r = runs[i];
+    const bool src_in = r.src >= base && r.bytes <= extent && static_cast<uint64_t>(r.src - base) <= extent - r.bytes;
+    const bool dst_in = r.dst >= s.staging && r.bytes <= s.ring_bytes &&
+                        static_cast<uint64_t>(r.dst - s.staging) <= s.ring_bytes - r.bytes;
+    if (!src_in || !dst_in) return hipErrorInvalidValue;
+    list[i] = bsr::StageRun{dev + (r.src - base), r.dst, r.bytes};
+    bytes += r.bytes;
+  }
   hipEvent_t t0 = nullptr, t1 = nullptr;
   if (s.time_flags & BSR_FLAG_TIME_STAGE) {
     t0 = take_timing_event(c);
@@ -511,12 +534,13 @@ hipError_t stage_copy(bsr_ctx* c, Session& s, uint8_t* dst, const uint8_t* src, 
       t0 = t1 = nullptr;
     }
   }
-  const hipError_t e = bsr::launch_stage(bsr::StageParams{dev + (src - base), dst, bytes}, s.copy, t0, t1);
+  const hipError_t e = bsr::launch_stage(list, n, s.copy, t0, t1);
   if (e != hipSuccess) {
     if (t0) c->timing_pool.push_back(t0);
     if (t1) c->timing_pool.push_back(t1);
     return e;
   }
+  *done = n;
   if (t0) s.stage_timing.emplace_back(t0, t1);
   ++s.st.n_stage_launches;
   s.st.stage_bytes += bytes;
@@ -1451,49 +1475,54 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
   const uint64_t deadline = c->cfg.window_timeout_ms ? t_window + static_cast<uint64_t>(c->cfg.window_timeout_ms) * 1000000ull : 0;
 
   // Consecutive chunks whose pinned sources are adjacent in the arena and
-  // whose slots are adjacent in the ring are staged by one copy: every copy
-  // pays a fixed start-up cost (a kernel launch, or the copy engine's own)
-  // that a 16 MB chunk does not amortise.  A run waits once, for the release its first
-  // chunk needs; a chunk needing a later release starts a new run, so no
-  // copy waits longer than it would alone.  A run is always issued before
-  // the batch holding its chunks is flushed, so the batch's copy event
-  // covers it.
-  struct Run {
-    const uint8_t* src = nullptr;
-    uint8_t* dst = nullptr;
-    uint64_t bytes = 0;
-    int64_t need = -1;
-    uint32_t first = 0, count = 0;
-  } run;
-  auto issue_run = [&]() -> hipError_t {
-    if (!run.count) return hipSuccess;
+  // whose slots are adjacent in the ring form a run, and the runs of an
+  // install batch (or of the rest of this call) are staged together: by one
+  // k_stage launch, or by one copy of the copy engine per run.  Every launch
+  // costs about 3 us of link time at its ends, and every copy of the copy
+  // engine tens of us; a chunk alone is 607 KB (14 us at 43 GB/s) with
+  // 16-token chunks and 2.4 MB (45.5 us at 53.3 GB/s) with 64-token ones,
+  // against 57.5 GB/s in large launches.  Chunks are not adjacent when they
+  // were stored one by one among others, or when a slot is no multiple of the
+  // arena's 4 KiB blocks.  A launch waits once, for the release its first
+  // chunk needs; a chunk needing a later release starts a new launch, so no
+  // copy waits longer than it would alone.  Runs are always staged before
+  // the batch holding their chunks is flushed, so the batch's copy event
+  // covers them.
+  Run runs[bsr::kStageMaxRuns];
+  uint32_t n_runs = 0;
+  int64_t runs_need = -1;  // release event the pending runs wait for
+  auto issue_runs = [&](uint32_t* done) -> hipError_t {
+    *done = 0;
+    if (!n_runs) return hipSuccess;
     hipError_t e = hipSuccess;
-    if (!s.one_stream && run.need >= 0 && run.need > s.copy_waited_seq) {
-      e = hipStreamWaitEvent(s.copy, res.free_ev[run.need % E], 0);
+    if (!s.one_stream && runs_need >= 0 && runs_need > s.copy_waited_seq) {
+      e = hipStreamWaitEvent(s.copy, res.free_ev[runs_need % E], 0);
       if (e != hipSuccess) return e;
-      s.copy_waited_seq = run.need;
+      s.copy_waited_seq = runs_need;
     }
-    e = stage_copy(c, s, run.dst, run.src, run.bytes, c->store.arena, c->store.arena_dev, c->store.arena_bytes);
-    if (e == hipSuccess) run = Run{};
+    e = stage_copy(c, s, runs, n_runs, c->store.arena, c->store.arena_dev, c->store.arena_bytes, done);
+    if (e == hipSuccess) n_runs = 0;
     return e;
   };
-  // A run whose copy could not be enqueued leaves the batch again: its chunks
-  // were never staged.
-  auto fail_run = [&](hipError_t e) -> int {
+  // Runs whose copies could not be enqueued leave the batch again: their
+  // chunks were never staged.
+  auto fail_runs = [&](hipError_t e, uint32_t done) -> int {
     const std::string why = hipGetErrorString(e);
-    const uint32_t first = run.first;
-    for (uint32_t k = 0; k < run.count; ++k) {
-      batch.pop_back();
-      s.pend_tags.pop_back();
-    }
-    run = Run{};
+    const uint32_t first = runs[done].first;
+    for (uint32_t j = done; j < n_runs; ++j)
+      for (uint32_t k = 0; k < runs[j].count; ++k) {
+        batch.pop_back();
+        s.pend_tags.pop_back();
+      }
+    n_runs = 0;
     if (int r2 = flush_batch(c, s)) return launch_failed(c, s, r2);
     fail_with(BSR_E_TRANSFER, "chunk %u: staging copy failed: %s", first, why.c_str());
     return host_fail(c, s, BSR_FAIL_TRANSFER, first, all_mask, BSR_E_TRANSFER);
   };
-  // install what is staged so far: the pending run's copy first
+  uint32_t done = 0;
+  // install what is staged so far: the pending runs' copies first
   auto flush_all = [&]() -> int {
-    if (hipError_t e = issue_run()) return fail_run(e);
+    if (hipError_t e = issue_runs(&done)) return fail_runs(e, done);
     if (int r2 = flush_batch(c, s)) return launch_failed(c, s, r2);
     return BSR_OK;
   };
@@ -1577,36 +1606,37 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
     uint8_t* dst = s.staging + static_cast<uint64_t>(slot) * c->geo.slot_bytes;
     hipError_t e = hipSuccess;
     if (!from_file && src_block) {
-      // pinned, one block: extend the run or start a new one
+      // pinned, one block: extend the last run, or start a new one beside it
       const int64_t need = need_seq > s.copy_waited_seq ? need_seq : -1;  // -1: nothing left to wait for
-      const bool extends = run.count && run.src + run.bytes == src_block && run.dst + run.bytes == dst &&
-                           need <= run.need;
-      if (!extends) {
-        if ((e = issue_run())) return fail_run(e);
-        run.src = src_block;
-        run.dst = dst;
-        run.first = i;
-        run.need = need_seq > s.copy_waited_seq ? need_seq : -1;  // issue_run may have waited
+      if (n_runs && need > runs_need)
+        if ((e = issue_runs(&done))) return fail_runs(e, done);
+      Run* last = n_runs ? &runs[n_runs - 1] : nullptr;
+      if (last && last->src + last->bytes == src_block && last->dst + last->bytes == dst) {
+        last->bytes += c->geo.slot_bytes;
+        ++last->count;
+      } else {
+        if (n_runs == bsr::kStageMaxRuns)
+          if ((e = issue_runs(&done))) return fail_runs(e, done);
+        if (!n_runs) runs_need = need_seq > s.copy_waited_seq ? need_seq : -1;  // issue_runs may have waited
+        runs[n_runs++] = Run{src_block, dst, c->geo.slot_bytes, i, 1};
       }
-      run.bytes += c->geo.slot_bytes;
-      ++run.count;
     } else {
-      if ((e = issue_run())) return fail_run(e);
+      if ((e = issue_runs(&done))) return fail_runs(e, done);
       if (need_seq >= 0 && need_seq > s.copy_waited_seq) {
         if ((rc = hip_check(hipStreamWaitEvent(s.copy, res.free_ev[need_seq % E], 0), "hipStreamWaitEvent(free)")))
           return launch_failed(c, s, rc);
         s.copy_waited_seq = need_seq;
       }
-      if (src_block && from_file) {
-        e = stage_copy(c, s, dst, src_block, c->geo.slot_bytes, c->ftier.bounce_base(bounce),
-                       c->ftier.bounce_device(bounce), c->ftier.file_bytes());
-      } else if (src_block) {
-        e = stage_copy(c, s, dst, src_block, c->geo.slot_bytes, c->store.arena, c->store.arena_dev,
-                       c->store.arena_bytes);
-      } else {
-        for (uint32_t g = 0; g < G && e == hipSuccess; ++g)
-          e = stage_copy(c, s, dst + c->geo.offset[g], c->store.block_ptr(ent[g].block) + c->geo.offset[g],
-                         c->geo.payload[g], c->store.arena, c->store.arena_dev, c->store.arena_bytes);
+      if (from_file) {
+        const Run r{src_block, dst, c->geo.slot_bytes, i, 1};
+        e = stage_copy(c, s, &r, 1, c->ftier.bounce_base(bounce), c->ftier.bounce_device(bounce),
+                       c->ftier.file_bytes(), &done);
+      } else {  // the chunk's groups lie in different blocks of the arena
+        Run parts[BSR_MAX_GROUPS];
+        for (uint32_t g = 0; g < G; ++g)
+          parts[g] = Run{c->store.block_ptr(ent[g].block) + c->geo.offset[g], dst + c->geo.offset[g],
+                         c->geo.payload[g], i, 1};
+        e = stage_copy(c, s, parts, G, c->store.arena, c->store.arena_dev, c->store.arena_bytes, &done);
       }
       if (e == hipSuccess && from_file) {
         // the bounce buffer is free again once this copy has run
@@ -1637,7 +1667,7 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
     if (batch.size() == s.batch)
       if ((rc = flush_all())) return rc;
   }
-  if (hipError_t e = issue_run()) return fail_run(e);  // nothing of this call stays unstaged
+  if (hipError_t e = issue_runs(&done)) return fail_runs(e, done);  // nothing of this call stays unstaged
   if (first_chunk + n_chunks == s.n_hit)
     if ((rc = flush_batch(c, s))) return launch_failed(c, s, rc);  // the prefix is complete
   s.next_chunk = first_chunk + n_chunks;
@@ -2012,7 +2042,8 @@ int bsr_measure_stage(bsr_ctx* c, uint64_t bytes, uint32_t reps, double* gbps) {
     double best = 0;
     for (uint32_t r = 0; r < reps && !rc; ++r) {
       rc = hip_check(hipEventRecord(ev[0], st), "hipEventRecord");
-      if (!rc) rc = hip_check(bsr::launch_stage(bsr::StageParams{static_cast<const uint8_t*>(hd), static_cast<uint8_t*>(d), bytes}, st), "staging copy");
+      const bsr::StageRun whole{static_cast<const uint8_t*>(hd), static_cast<uint8_t*>(d), bytes};
+      if (!rc) rc = hip_check(bsr::launch_stage(&whole, 1, st), "staging copy");
       if (!rc) rc = hip_check(hipEventRecord(ev[1], st), "hipEventRecord");
       if (!rc) rc = hip_check(hipEventSynchronize(ev[1]), "hipEventSynchronize");
       float ms = 0;

@@ -16,6 +16,7 @@ from oracle_side import build_case
 from paper_2608_17826_amd import bsr
 from paper_2608_17826_amd.session import RestoreSession, group_dsts
 from workloads import generate, get_config
+from workloads.configs import GroupSpec, Workload
 from workloads.device import place
 from workloads.gen import random_workload
 
@@ -171,5 +172,29 @@ def test_timing_flags_are_taken_at_bind():
         assert st["install_ms_total"] > 0 and st["stage_ms_total"] == 0
         with pytest.raises(bsr.BsrError):
             bsr.bsr_set_timing(gc.ctx, bsr.BSR_FLAG_SDMA_COPIES)
+    finally:
+        gc.close()
+
+
+# (record bytes, chunk tokens): slots of 256 B, one tile (4,096 B), a tile and
+# one 256 B part, and three tiles and a part, none adjacent in the arena but
+# the second
+@pytest.mark.parametrize("flags", [0, bsr.BSR_FLAG_TWO_STREAMS])
+@pytest.mark.parametrize("record,C,W", [(4, 8, 3), (128, 32, 8), (124, 35, 40), (1152, 11, 33)])
+def test_runs_of_a_scattered_store(record, C, W, flags):
+    """Chunks stored one by one in a random order, so that a staging launch
+    takes many runs (up to 32, in one window of more) and runs of one to a
+    few chunks; the image is the oracle's."""
+    w = Workload(index=400 + record, name="runs", n_tokens=70 * C + 3, chunk_tokens=C,
+                 groups=(GroupSpec("g", 8, 1, record, value_kind="bytes"),), windows=(W,), pool_factor=2)
+    wi = generate(w)
+    case, n, res = _oracle(wi, W)
+    say(f"case: 70 chunks of {bsr.bsr_slot_bytes(layout_of(wi))} B stored in random order, W={W}, flags={flags}")
+    gc = GpuCase(wi, W=W, flags=flags, pinned_chunks=[], arena_chunks=72)
+    try:
+        for i in np.random.default_rng(record).permutation(70):
+            bsr.bsr_store_put_chunk(gc.ctx, int(gc.keys[i]), wi.payloads(int(i)))
+        assert gc.probe(5)[0] == n == 70
+        _check(wi, case, res, gc.restore(5, n), gc.dev.pools, gc.dev.valid)
     finally:
         gc.close()
