@@ -109,9 +109,11 @@ extern "C" {
                                       nothing exposed; the kernels never write such an id).  The caller
                                       guarantees that no id repeats within one group's prefix (not checked) */
 #define BSR_FLAG_TWO_STREAMS 8u   /* stage every request on the copy stream.  By default a request of at
-                                      most 64 MiB of chunks is staged on the compute stream, so that stream
+                                      most 64 MiB of chunks stays on the compute stream, so that stream
                                       order, not events between the two streams, orders its copies,
-                                      installs and slot reuse */
+                                      installs and slot reuse; its chunks in a pinned arena are installed
+                                      straight from there, with no staging copy (each still counts as one
+                                      live slot of the ring, which is provided as for any request) */
 #define BSR_FLAG_SDMA_COPIES 4u   /* stage chunks with the copy engine (hipMemcpyAsync) instead of the
                                       library's staging-copy kernel.  By default a small kernel on the copy
                                       stream reads each run of chunks from pinned host memory (the library's
@@ -212,7 +214,7 @@ typedef struct bsr_stats {
   uint64_t request_id;
   uint32_t n_hit_chunks;        /* n: prefix length bound for restore */
   uint32_t window_chunks;       /* W */
-  uint32_t install_batch;       /* chunks per install launch */
+  uint32_t install_batch;       /* chunks per install launch, at most */
   uint32_t n_windows;           /* restore_window calls accepted */
   uint32_t n_chunks_enqueued;   /* chunks whose copy and install were enqueued */
   uint32_t n_install_launches;
@@ -231,11 +233,13 @@ typedef struct bsr_stats {
   uint64_t probe_ns;               /* host time of the last probe */
   uint64_t enqueue_ns;             /* host time spent inside restore_window calls */
   uint64_t commit_wait_ns;         /* host time commit waited for the device */
-  double install_ms_total;         /* sum of install-kernel durations (BSR_FLAG_TIME_INSTALL) */
+  double install_ms_total;         /* sum of install-kernel durations (BSR_FLAG_TIME_INSTALL); with the
+                                      host link's time where they read pinned memory */
   double install_ms_max;           /* longest install launch (BSR_FLAG_TIME_INSTALL) */
   uint64_t host_bounce_bytes;      /* pinned host landing zone of the file tier (when it served chunks) */
   uint32_t file_tier_chunks;       /* chunks restored from the file tier */
-  uint32_t n_stage_launches;       /* staging-copy kernel launches (0 when the copy engine staged) */
+  uint32_t n_stage_launches;       /* staging-copy kernel launches (0 when the copy engine staged, or when
+                                      the chunks were installed straight from pinned memory) */
   uint64_t stage_bytes;            /* bytes those launches moved from pinned host memory */
   double stage_ms_total;           /* sum of their durations (BSR_FLAG_TIME_STAGE) */
 } bsr_stats;
@@ -453,7 +457,8 @@ int bsr_request_bind(bsr_ctx* ctx, uint64_t request_id, uint32_t n_hit_chunks,
  * yet requested).  Asynchronous: for each chunk it looks the entries up
  * (a missing entry, an injected delay beyond the window deadline, or a
  * failed copy submission fails the window), waits for the chunk's slot to be
- * released, and enqueues the pinned-host -> slot copy on copy_stream; per
+ * released, and enqueues the pinned-host -> slot copy on copy_stream (a small
+ * request's install reads pinned memory itself, see BSR_FLAG_TWO_STREAMS); per
  * install batch (which may span windows: chunks left over at the end of a
  * call join the next call's batch, and every later call of the request --
  * commit, invalidate, mark, end -- installs them first) it enqueues the

@@ -215,13 +215,40 @@ struct InstallParams {
   InstallGroup g[BSR_MAX_GROUPS];  // in dispatch order
 };
 
-// Device words the verify kernel uses across workgroups (library-owned,
-// zeroed by the begin kernel and left zeroed by every verify launch).
+// Device words that the workgroups of a launch share to check its tags
+// (library-owned, zeroed by the begin kernel and left zeroed by every launch).
 struct VerifyAux {
   uint32_t bad[BSR_MAX_INSTALL_BATCH];  // per chunk of the launch: mask of mismatching groups
   uint32_t arrivals;                    // workgroups finished in the current launch
   uint32_t pad[15];
+  // direct installs: per (chunk, group), the sum and XOR of the words
+  // installed, less and XORed with the stored tag
+  TagPair acc[BSR_MAX_INSTALL_BATCH * BSR_MAX_GROUPS];
 };
+
+// Install straight from pinned memory: chunk first_chunk + c is read at
+// src[c], the device's view of its slot-shaped source (16-byte aligned), and
+// the launch checks its tags itself.
+struct DirectParams {
+  InstallParams ip;
+  const uint8_t* src[BSR_MAX_INSTALL_BATCH];
+  bsr_dev_status* status;
+  VerifyAux* aux;
+  uint64_t expected[BSR_MAX_INSTALL_BATCH][BSR_MAX_GROUPS];  // stored tags
+};
+// Its grid: workgroups that take pieces in turn, as many as hold
+// kDirectInflight bytes of loads between them at the launch's average piece,
+// at least kDirectMinGrid and two pieces each, at most kDirectMaxGrid.  The
+// link needs some 200 KB in flight, but a workgroup loads nothing while it
+// decodes and stores, and small pieces keep few bytes in flight each.
+// Measured in us per request on one box (kDirectInflight 256 KiB / 512 KiB /
+// 1 MiB / 2 MiB): 63 MB of 8 KiB pieces 1,227 / 1,199 / 1,185 / 1,192; 20 MB
+// of eight groups' pieces, 1.9 KB on average, 717 / 691 / 639 / 652; one
+// workgroup per piece instead loses link rate at its start (a staging kernel
+// with 8 MB in flight moves 2.3 MB at 40 GB/s, one with 192 KiB at 50).
+constexpr uint64_t kDirectInflight = 1u << 20;
+constexpr uint64_t kDirectMinGrid = 64;
+constexpr uint64_t kDirectMaxGrid = 512;
 
 struct VerifyParams {
   const TagPair* partials;
@@ -337,6 +364,8 @@ hipError_t launch_scatter(const ScatterParams& p, hipStream_t s);
 
 hipError_t launch_install(const InstallParams& p, uint32_t n_workgroups, hipStream_t s,
                           hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
+hipError_t launch_install_direct(const DirectParams& p, hipStream_t s, hipEvent_t start = nullptr,
+                                 hipEvent_t stop = nullptr);
 hipError_t launch_verify(const VerifyParams& p, hipStream_t s);
 hipError_t launch_stage(const StageRun* runs, uint32_t n_runs, hipStream_t s, hipEvent_t start = nullptr,
                         hipEvent_t stop = nullptr);

@@ -19,6 +19,9 @@
 //           a values plane and a scales plane inside a block) stage the
 //           piece in LDS and write both planes with coalesced stores.  Every
 //           wave folds the words it read into a (sum, xor) tag partial.
+// direct  : the install of a small request, reading pinned memory over the
+//           host link itself (no staging copy, no ring), and checking its
+//           tags in the same launch.
 // verify  : reduce the partials of each (chunk, group) and compare with the
 //           tag recorded at store time; the first mismatching chunk, in
 //           chunk order, fails the request (q_g = 0 for its mismatching
@@ -195,18 +198,30 @@ __device__ __forceinline__ uint32_t wave_xor(uint32_t v) {
 
 // ---------------------------------------------------------------------------
 // contiguous piece that is not 16-byte aligned (records are multiples of 4
-// bytes): 4-byte words
+// bytes): 4-byte words, kUnroll of them in flight per thread
 // ---------------------------------------------------------------------------
+template <uint32_t kUnroll>
 __device__ __forceinline__ void copy_words(const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
                                            uint32_t len, uint32_t tid, uint32_t& s, uint32_t& x) {
   const uint32_t* s1 = reinterpret_cast<const uint32_t*>(src);
   uint32_t* d1 = reinterpret_cast<uint32_t*>(dst);
   const uint32_t nw = len >> 2;
-  for (uint32_t i = tid; i < nw; i += kInstallThreads) {
-    const uint32_t w = *global_ptr(s1 + i);
-    s += w;
-    x ^= w;
-    *global_ptr(d1 + i) = w;
+  for (uint32_t base = 0; base < nw; base += kUnroll * kInstallThreads) {
+    uint32_t w[kUnroll];
+#pragma unroll
+    for (uint32_t u = 0; u < kUnroll; ++u) {  // lanes past the end reload the last word
+      const uint32_t i = base + u * kInstallThreads + tid;
+      w[u] = *global_ptr(s1 + (i < nw ? i : nw - 1));
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kUnroll; ++u) {
+      const uint32_t i = base + u * kInstallThreads + tid;
+      if (i < nw) {
+        s += w[u];
+        x ^= w[u];
+        *global_ptr(d1 + i) = w[u];
+      }
+    }
   }
 }
 
@@ -271,6 +286,7 @@ __device__ __forceinline__ void planar_from_regs(const u32x4 (&v)[kPlanarVecs], 
 }
 
 // Any alignment: 4-byte words straight from the staged records.
+template <uint32_t kUnroll>
 __device__ __forceinline__ void planar_words(const uint8_t* __restrict__ src, uint8_t* dst1, uint8_t* dst2,
                                              uint32_t mu, uint32_t r, uint32_t sp, uint32_t tid, uint32_t& s,
                                              uint32_t& x) {
@@ -278,16 +294,27 @@ __device__ __forceinline__ void planar_words(const uint8_t* __restrict__ src, ui
   uint32_t* d1 = reinterpret_cast<uint32_t*>(dst1);
   uint32_t* d2 = reinterpret_cast<uint32_t*>(dst2);
   const uint32_t rw = r >> 2, sw = sp >> 2, nw = (mu * r) >> 2;
-  for (uint32_t i = tid; i < nw; i += kInstallThreads) {
-    const uint32_t u = i / rw;
-    const uint32_t wi = i - u * rw;
-    const uint32_t w = *global_ptr(s1 + i);
-    s += w;
-    x ^= w;
-    if (wi < sw)
-      *global_ptr(d1 + u * sw + wi) = w;
-    else
-      *global_ptr(d2 + u * (rw - sw) + (wi - sw)) = w;
+  for (uint32_t base = 0; base < nw; base += kUnroll * kInstallThreads) {
+    uint32_t w[kUnroll];
+#pragma unroll
+    for (uint32_t v = 0; v < kUnroll; ++v) {  // lanes past the end reload the last word
+      const uint32_t i = base + v * kInstallThreads + tid;
+      w[v] = *global_ptr(s1 + (i < nw ? i : nw - 1));
+    }
+#pragma unroll
+    for (uint32_t v = 0; v < kUnroll; ++v) {
+      const uint32_t i = base + v * kInstallThreads + tid;
+      if (i < nw) {
+        const uint32_t u = i / rw;
+        const uint32_t wi = i - u * rw;
+        s += w[v];
+        x ^= w[v];
+        if (wi < sw)
+          *global_ptr(d1 + u * sw + wi) = w[v];
+        else
+          *global_ptr(d2 + u * (rw - sw) + (wi - sw)) = w[v];
+      }
+    }
   }
 }
 
@@ -339,11 +366,12 @@ union ArgWords {
   T s;
 };
 
+#define BSR_KERNARG __attribute__((address_space(4)))
 template <typename T>
-__device__ __forceinline__ T load_args(const T* src) {
+__device__ __forceinline__ T load_args(const BSR_KERNARG T* src) {
   static_assert(sizeof(T) == sizeof(u32x16) * 2, "argument blocks are 128 bytes");
   ArgWords<T> w;
-  const u32x16* v = reinterpret_cast<const u32x16*>(src);
+  const BSR_KERNARG u32x16* v = reinterpret_cast<const BSR_KERNARG u32x16*>(src);
   w.v[0] = v[0];
   w.v[1] = v[1];
   return w.s;
@@ -358,15 +386,19 @@ __device__ __forceinline__ uint32_t add_if_ge(uint32_t acc, uint32_t a, uint32_t
   return acc;
 }
 
-__global__ __launch_bounds__(kInstallThreads) void k_install(const InstallParams p) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-
-  const uint32_t tid = threadIdx.x;
+// One work item.  bid: its index in dispatch order.  kDirect: the chunk is
+// read from chunk_src[c] (the device's view of pinned memory) instead of its
+// ring slot, and the words' sum and XOR go to acc[c][group], in LDS, instead
+// of a tag partial.
+template <bool kDirect>
+__device__ __forceinline__ void install_piece(const InstallHead& H, const BSR_KERNARG InstallGroup* groups,
+                                              const uint8_t* const BSR_KERNARG* chunk_src, TagPair* acc, uint32_t bid,
+                                              uint8_t* lds, uint32_t tid) {
   const uint32_t lane = tid & 63;
-  const InstallHead H = load_args(&p.h);
-  // work index -> dispatch position (the group), then (chunk, piece within
-  // the chunk's group range)
-  const uint32_t bid = xcd_work_index(blockIdx.x, H.xcd_full, H.xcd_log2);
+  // words in flight per thread of an unaligned piece: over the link a whole
+  // contiguous piece, out of HBM enough to leave the registers of the main
+  // path alone
+  constexpr uint32_t kWords = kDirect ? kMaxPieceBytes / (4 * kInstallThreads) : 4;
   // Every wave runs this decode before its first data load, and that delay
   // costs bandwidth, so it is kept short: about 120 scalar instructions
   // (256 extra ones per wave cost a plain copy of this shape about 3 points
@@ -376,7 +408,7 @@ __global__ __launch_bounds__(kInstallThreads) void k_install(const InstallParams
   uint32_t oi = 0;
 #pragma unroll
   for (uint32_t q = 1; q < BSR_MAX_GROUPS; ++q) oi = add_if_ge(oi, bid, H.start[q]);
-  const InstallGroup G = load_args(&p.g[oi]);
+  const InstallGroup G = load_args(&groups[oi]);
   uint32_t rem = bid - H.n_chunks * G.prefix;
   const uint32_t cf = packed_div(G.div_per_chunk.m, G.div_per_chunk.s, rem);
   rem -= cf * G.per_chunk;
@@ -389,8 +421,14 @@ __global__ __launch_bounds__(kInstallThreads) void k_install(const InstallParams
   const uint32_t j = r1 - t * G.segs_per_chunk;
 
   const uint32_t chunk = H.first_chunk + c;
-  const uint32_t slot0 = H.first_slot + c;  // c < n_chunks <= W
-  const uint32_t slot = slot0 >= H.window ? slot0 - H.window : slot0;
+  const uint8_t* base;
+  if constexpr (kDirect) {
+    base = chunk_src[c];
+  } else {
+    const uint32_t slot0 = H.first_slot + c;  // c < n_chunks <= W
+    const uint32_t slot = slot0 >= H.window ? slot0 - H.window : slot0;
+    base = H.ring + static_cast<uint64_t>(slot) * H.slot_bytes;
+  }
   // Token positions in 32 bits: the bound prefix plus two blocks stays
   // below 2^32 tokens (checked when the request is bound).
   const uint32_t C = H.chunk_tokens, B = G.block_tokens;
@@ -408,7 +446,7 @@ __global__ __launch_bounds__(kInstallThreads) void k_install(const InstallParams
     const uint32_t o0 = lo - blo;
     // offsets inside a slot and inside a block fit 32 bits (slot < 4 GiB,
     // block < 2 GiB)
-    const uint8_t* src = H.ring + static_cast<uint64_t>(slot) * H.slot_bytes + (G.staged_off + (t * C + q0) * r);
+    const uint8_t* src = base + (G.staged_off + (t * C + q0) * r);
     if (G.kind == BSR_KIND_CONTIG) {
       const uint32_t seg = m * r;
       const uint32_t off = piece * G.piece;
@@ -448,7 +486,7 @@ __global__ __launch_bounds__(kInstallThreads) void k_install(const InstallParams
             }
           }
         } else {
-          copy_words(sp, dp, len, tid, s, x);
+          copy_words<kWords>(sp, dp, len, tid, s, x);
         }
       }
     } else {
@@ -478,22 +516,117 @@ __global__ __launch_bounds__(kInstallThreads) void k_install(const InstallParams
         uint8_t* blk = md.tensor_base + static_cast<uint64_t>(md.block) * G.block_bytes;
         uint8_t* dst1 = blk + (o0 + u0) * sp;
         uint8_t* dst2 = blk + (B * sp + (o0 + u0) * (r - sp));
+        if constexpr (kDirect) __syncthreads();  // the workgroup's previous piece has left the LDS
         if (src_ok && ((reinterpret_cast<uintptr_t>(dst1) & 15u) | (reinterpret_cast<uintptr_t>(dst2) & 3u)) == 0)
           planar_from_regs(v, nvec, dst1, dst2, mu, r, sp, G.div_p1, G.div_p2, lds, tid, s, x);
         else
-          planar_words(psrc, dst1, dst2, mu, r, sp, tid, s, x);
+          planar_words<kWords>(psrc, dst1, dst2, mu, r, sp, tid, s, x);
       }
     }
   }
 
-  // one tag partial per wave
   s = wave_sum(s);
   x = wave_xor(x);
-  // TagPair {sum, xor} as one little-endian 8-byte word
-  static_assert(sizeof(TagPair) == 8 && offsetof(TagPair, x) == 4, "sum in the low word");
-  if (lane == 0)
-    *global_ptr(reinterpret_cast<uint64_t*>(H.partials) + wg * kInstallWaves + (tid >> 6)) =
-        static_cast<uint64_t>(s) | (static_cast<uint64_t>(x) << 32);
+  if constexpr (kDirect) {
+    if (lane == 0) {
+      TagPair* a = acc + c * BSR_MAX_GROUPS + G.group;
+      atomicAdd(&a->sum, s);
+      atomicXor(&a->x, x);
+    }
+  } else {
+    // one tag partial per wave: TagPair {sum, xor} as one little-endian 8-byte word
+    static_assert(sizeof(TagPair) == 8 && offsetof(TagPair, x) == 4, "sum in the low word");
+    if (lane == 0)
+      *global_ptr(reinterpret_cast<uint64_t*>(H.partials) + wg * kInstallWaves + (tid >> 6)) =
+          static_cast<uint64_t>(s) | (static_cast<uint64_t>(x) << 32);
+  }
+}
+
+__global__ __launch_bounds__(kInstallThreads) void k_install(const InstallParams p) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const auto* q = (const BSR_KERNARG InstallParams*)(__builtin_amdgcn_kernarg_segment_ptr());
+  const InstallHead H = load_args(&q->h);
+  // work index -> dispatch position (the group), then (chunk, piece within
+  // the chunk's group range)
+  install_piece<false>(H, q->g, nullptr, nullptr, xcd_work_index(blockIdx.x, H.xcd_full, H.xcd_log2), lds, threadIdx.x);
+}
+
+// The same work with no ring in between: chunks go from pinned memory over
+// the host link straight into their blocks.  For requests on one stream, where
+// staging copy, install and verify run one after the other: three launches,
+// about 10 us apart, become one, and the install's own time goes.  Bound by
+// the link, so a small grid takes the pieces in turn, one piece of loads in
+// flight per workgroup.  Measured in turn with the three launches: 1K tokens
+// in 147 KB chunks at W = 2 (2.4 MB) 176 -> 96 us per request, 1,287 tokens of
+// eight ragged groups (3.5 MB) 249 -> 133 us, 63 MB of 64-token chunks 1,268
+// -> 1,180 us.  The launch verifies itself: a workgroup sums the tags of
+// its pieces per (chunk, group) in LDS and adds them to the shared words when
+// it is done; the first workgroup also takes the stored tags off, so a
+// matching entry ends at zero, and the last one to finish applies the first
+// mismatching chunk as k_verify does.
+__global__ __launch_bounds__(kInstallThreads) void k_install_direct(const DirectParams p) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  __shared__ TagPair acc[BSR_MAX_INSTALL_BATCH * BSR_MAX_GROUPS];
+  __shared__ uint32_t bad[BSR_MAX_INSTALL_BATCH];
+  __shared__ uint32_t is_last;
+  const uint32_t tid = threadIdx.x, n_chunks = p.ip.h.n_chunks, n_acc = n_chunks * BSR_MAX_GROUPS;
+  for (uint32_t i = tid; i < n_acc; i += kInstallThreads) {
+    TagPair t{0u, 0u};
+    if (blockIdx.x == 0 && i % BSR_MAX_GROUPS < p.ip.h.n_groups) {
+      const uint64_t e = p.expected[i / BSR_MAX_GROUPS][i % BSR_MAX_GROUPS];
+      t = TagPair{0u - static_cast<uint32_t>(e), static_cast<uint32_t>(e >> 32)};
+    }
+    acc[i] = t;
+  }
+  if (tid < BSR_MAX_INSTALL_BATCH) bad[tid] = 0;
+  __syncthreads();
+  const uint32_t total = n_chunks * p.ip.h.wg_per_chunk, grid = gridDim.x;
+  for (uint32_t b = blockIdx.x; b < total; b += grid) {
+    // The arguments are read again for every piece: kept across the loop, they
+    // take more scalar registers than there are.
+    const auto* q = (const BSR_KERNARG DirectParams*)(__builtin_amdgcn_kernarg_segment_ptr());
+    asm volatile("" : "+s"(q));
+    const InstallHead H = load_args(&q->ip.h);
+    install_piece<true>(H, q->ip.g, q->src, acc, b, lds, tid);
+  }
+  __syncthreads();
+  VerifyAux* aux = p.aux;
+  for (uint32_t i = tid; i < n_acc; i += kInstallThreads) {
+    const TagPair t = acc[i];
+    if (t.sum) atomicAdd(&aux->acc[i].sum, t.sum);
+    if (t.x) atomicXor(&aux->acc[i].x, t.x);
+  }
+  // Everything the workgroups share is read and written by atomics, which act
+  // at the device's point of coherence: it is enough that this wave's have
+  // been performed before the workgroup is counted (a device-scope fence
+  // would write back the XCD's L2 in every workgroup: 40 us of a 20 MB
+  // request of small pieces).
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) is_last = atomicAdd(&aux->arrivals, 1u) == grid - 1;
+  __syncthreads();
+  if (!is_last) return;
+  for (uint32_t i = tid; i < n_acc; i += kInstallThreads)
+    if (atomicExch(reinterpret_cast<unsigned long long*>(&aux->acc[i]), 0ull) != 0ull)
+      atomicOr(&bad[i / BSR_MAX_GROUPS], 1u << (i % BSR_MAX_GROUPS));
+  __syncthreads();
+  if (tid < 64) {
+    // the install's own prefix test, as in k_verify; only this thread block
+    // writes the status words, and only here
+    bsr_dev_status* st = p.status;
+    const uint32_t n_groups = p.ip.h.n_groups;
+    bool live = st->fail == 0;
+    for (uint32_t g = 0; g < n_groups; ++g) live = live && st->q[g] != 0;
+    const uint32_t m = tid < n_chunks ? bad[tid] : 0u;
+    const uint64_t any = __ballot(m != 0u);
+    if (live && any != 0ull && tid == static_cast<uint32_t>(__builtin_ctzll(any))) {
+      st->fail = BSR_FAIL_CORRUPT;
+      st->first_failed_chunk = p.ip.h.first_chunk + tid;
+      for (uint32_t g = 0; g < n_groups; ++g)
+        if ((m >> g) & 1u) st->q[g] = 0;
+    }
+    if (tid == 0) atomicExch(&aux->arrivals, 0u);
+  }
 }
 
 // One workgroup per (chunk, group) of the launch reduces that entry's wave
@@ -610,9 +743,11 @@ __global__ __launch_bounds__(256) void k_finish(const FinishParams p) {
       st->fallback = 0;
       st->phase = 1;
       st->reserved[0] = st->reserved[1] = 0;
-      for (int i = 0; i < BSR_MAX_INSTALL_BATCH; ++i) p.verify_aux->bad[i] = 0;
-      p.verify_aux->arrivals = 0;
     }
+    static_assert(sizeof(VerifyAux) % 4 == 0, "cleared word by word");
+    if (blockIdx.x == 0)
+      for (uint32_t i = threadIdx.x; i < sizeof(VerifyAux) / 4; i += blockDim.x)
+        reinterpret_cast<uint32_t*>(p.verify_aux)[i] = 0;
     value = 0;
   } else if (p.mode == kFinishCommit) {
     bool Q = st->fail == BSR_FAIL_NONE;
@@ -820,6 +955,21 @@ hipError_t launch_install(const InstallParams& p, uint32_t n_workgroups, hipStre
   } else {
     hipLaunchKernelGGL(k_install, dim3(n_workgroups), dim3(kInstallThreads), p.h.lds_bytes, s, p);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_install_direct(const DirectParams& p, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+  const uint64_t total = static_cast<uint64_t>(p.ip.h.n_chunks) * p.ip.h.wg_per_chunk;
+  if (p.ip.h.n_chunks == 0 || p.ip.h.n_chunks > BSR_MAX_INSTALL_BATCH || total >= (1ull << 31)) return hipErrorInvalidValue;
+  for (uint32_t i = 0; i < p.ip.h.n_chunks; ++i)
+    if (!p.src[i] || (reinterpret_cast<uintptr_t>(p.src[i]) & 15u)) return hipErrorInvalidValue;
+  const uint64_t bytes = p.ip.h.n_chunks * p.ip.h.slot_bytes;
+  const uint64_t want = std::min({kDirectMaxGrid, kDirectInflight * total / bytes + 1, total / 2});
+  const uint32_t grid = static_cast<uint32_t>(std::min(std::max(kDirectMinGrid, want), total));
+  if (start && stop)
+    hipExtLaunchKernelGGL(k_install_direct, dim3(grid), dim3(kInstallThreads), p.ip.h.lds_bytes, s, start, stop, 0, p);
+  else
+    hipLaunchKernelGGL(k_install_direct, dim3(grid), dim3(kInstallThreads), p.ip.h.lds_bytes, s, p);
   return hipGetLastError();
 }
 

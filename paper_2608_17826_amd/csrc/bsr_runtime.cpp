@@ -65,9 +65,16 @@ uint64_t now_ns() {
 }
 
 constexpr uint64_t kAlign = 256;
-// Requests of at most this many chunk bytes are staged on the compute stream
-// (Session::one_stream).
+// Requests of at most this many chunk bytes stay on the compute stream
+// (Session::one_stream): staged there, or, from pinned memory, installed with
+// no staging copy at all.
 constexpr uint64_t kOneStreamBytes = 64ull << 20;
+// Chunks that the install reads straight from pinned memory are launched at
+// the end of a window once they hold this many bytes, or else join the next
+// window's: a launch costs about 15 us beside its 18 us/MiB of link time.  The
+// 1K-token workload (295 KB windows) takes 132 us with a launch per window,
+// 111 with 512 KiB, 96 with 1 MiB and 99 in one launch, which starts late.
+constexpr uint64_t kDirectFlushBytes = 1ull << 20;
 // Install launches whose staged chunks exceed this many bytes walk their
 // chunks in alternate directions from one dispatch position to the next
 // (InstallHead::serpentine).  Measured on the 512K 4-group layout: launches
@@ -374,11 +381,15 @@ struct Session {  // one bound request
   uint32_t next_chunk = 0;
   bool failed = false;
   bool completing = false;  // a commit or end is waiting for its device work
-  // A small request is staged on the compute stream itself (copy == compute):
-  // stream order then does what the copy and release events do between two
-  // streams, without their hand-over latency.
+  // A small request stays on the compute stream (copy == compute): stream
+  // order then does what the copy and release events do between two streams,
+  // without their hand-over latency.
   bool one_stream = false;
   uint32_t batch = 0;       // chunks per install launch
+  // Chunks per install launch that reads pinned memory itself (requests on
+  // one stream, where a staging copy could not overlap an install anyway);
+  // 0: every chunk goes through the ring.
+  uint32_t batch_direct = 0;
   bool copy_dirty = false;  // the copy stream holds work no compute-stream wait covers yet
   uint32_t time_flags = 0;  // BSR_FLAG_TIME_INSTALL / BSR_FLAG_TIME_STAGE, taken at bind
   int host_fail = BSR_FAIL_NONE;
@@ -398,6 +409,7 @@ struct Session {  // one bound request
   // chunks copied but not yet installed (the current install batch)
   std::vector<uint32_t> pend;
   std::vector<std::array<uint64_t, BSR_MAX_GROUPS>> pend_tags;
+  std::vector<const uint8_t*> pend_src;  // their device-visible sources, when installed straight from pinned memory
   Inject inject;   // armed before this request was bound
   bsr_stats st{};  // this request's counters
 };
@@ -410,6 +422,7 @@ struct bsr_ctx {
   uint32_t W = 0;
   uint32_t batch = 0;      // chunks per install launch of a request staged on the copy stream
   uint32_t batch_one = 0;  // ... and of one staged on the compute stream
+  uint32_t batch_direct = 0;  // ... and of one installed straight from pinned memory
   int device = -1;
   std::mutex mu;
   Store store;
@@ -574,7 +587,10 @@ int flush_batch(bsr_ctx* c, Session& s) {
 
   // the kernel takes chunk first_chunk + c to slot first_slot + c, less W
   // once: a launch holds consecutive chunks, at most W of them
-  if (chunks.size() > s.window || chunks.back() - chunks.front() + 1 != chunks.size())
+  // (a direct launch uses no slot, so only the run matters)
+  const bool direct = !s.pend_src.empty();
+  if ((!direct && chunks.size() > s.window) || chunks.back() - chunks.front() + 1 != chunks.size() ||
+      (direct && s.pend_src.size() != chunks.size()))
     return fail_with(BSR_E_STATE, "install batch of %zu chunks is not a run of at most W = %u", chunks.size(), s.window);
   InstallParams ip = s.ip;
   ip.h.n_chunks = static_cast<uint32_t>(chunks.size());
@@ -593,7 +609,19 @@ int flush_batch(bsr_ctx* c, Session& s) {
       t0 = t1 = nullptr;
     }
   }
-  if ((rc = hip_check(bsr::launch_install(ip, ip.h.n_chunks * ip.h.wg_per_chunk, s.compute, t0, t1), "install launch"))) {
+  hipError_t launched;
+  if (direct) {
+    bsr::DirectParams dp{};
+    dp.ip = ip;
+    std::copy(s.pend_src.begin(), s.pend_src.end(), dp.src);
+    dp.status = s.status;
+    dp.aux = r.verify_aux;
+    for (size_t i = 0; i < chunks.size(); ++i) std::copy(tags[i].begin(), tags[i].end(), dp.expected[i]);
+    launched = bsr::launch_install_direct(dp, s.compute, t0, t1);
+  } else {
+    launched = bsr::launch_install(ip, ip.h.n_chunks * ip.h.wg_per_chunk, s.compute, t0, t1);
+  }
+  if ((rc = hip_check(launched, "install launch"))) {
     if (t0) c->timing_pool.push_back(t0);
     if (t1) c->timing_pool.push_back(t1);
     return rc;
@@ -605,22 +633,25 @@ int flush_batch(bsr_ctx* c, Session& s) {
   // the copy engine's path to the slots.
   if (!s.one_stream && (rc = hip_check(hipEventRecord(freed, s.compute), "hipEventRecord(free)"))) return rc;
   for (uint32_t ch : chunks) s.slot_free_seq[ch % s.window] = seq;
-  VerifyParams vp{};
-  vp.partials = r.partials;
-  vp.status = s.status;
-  vp.aux = r.verify_aux;
-  vp.n_chunks = ip.h.n_chunks;
-  vp.first_chunk = ip.h.first_chunk;
-  vp.n_groups = c->geo.L.n_groups;
-  vp.wg_per_chunk = ip.h.wg_per_chunk;
-  std::memcpy(vp.wg_start, c->geo.wg_start, sizeof vp.wg_start);
-  for (size_t i = 0; i < chunks.size(); ++i)
-    for (uint32_t g = 0; g < BSR_MAX_GROUPS; ++g) vp.expected[i][g] = tags[i][g];
-  if ((rc = hip_check(bsr::launch_verify(vp, s.compute), "verify launch"))) return rc;
+  if (!direct) {  // a direct launch has checked its tags itself
+    VerifyParams vp{};
+    vp.partials = r.partials;
+    vp.status = s.status;
+    vp.aux = r.verify_aux;
+    vp.n_chunks = ip.h.n_chunks;
+    vp.first_chunk = ip.h.first_chunk;
+    vp.n_groups = c->geo.L.n_groups;
+    vp.wg_per_chunk = ip.h.wg_per_chunk;
+    std::memcpy(vp.wg_start, c->geo.wg_start, sizeof vp.wg_start);
+    for (size_t i = 0; i < chunks.size(); ++i)
+      for (uint32_t g = 0; g < BSR_MAX_GROUPS; ++g) vp.expected[i][g] = tags[i][g];
+    if ((rc = hip_check(bsr::launch_verify(vp, s.compute), "verify launch"))) return rc;
+  }
   s.st.n_install_launches++;
   s.st.installed_bytes += static_cast<uint64_t>(chunks.size()) * c->geo.chunk_payload;
   chunks.clear();
   tags.clear();
+  s.pend_src.clear();
   return BSR_OK;
 }
 
@@ -799,6 +830,10 @@ static int ctx_create(const bsr_layout* layout, const bsr_config* config, bsr_ct
   c->batch_one = config->install_batch ? b : std::min(W ? W : 32u, static_cast<uint32_t>(BSR_MAX_INSTALL_BATCH));
   while (c->batch_one > b && static_cast<uint64_t>(c->batch_one) * c->geo.wg_per_chunk * bsr::kInstallThreads >= (1ull << 32))
     --c->batch_one;
+  // a direct launch holds no ring slot, so W does not bound it; a request on
+  // one stream has at most kOneStreamBytes of chunks to put into it
+  c->batch_direct = config->install_batch ? b : static_cast<uint32_t>(std::min<uint64_t>(
+      BSR_MAX_INSTALL_BATCH, std::max<uint64_t>(1, kOneStreamBytes / c->geo.slot_bytes)));
   c->device = config->hip_device;
   c->budget = B;
   c->store.index.resize(layout->n_groups);
@@ -1388,6 +1423,7 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
   s.one_stream = one_stream;
   s.time_flags = c->cfg.flags & kTimingFlags;
   s.batch = one_stream ? c->batch_one : c->batch;
+  s.batch_direct = one_stream && c->kernel_copies && c->store.arena_dev ? c->batch_direct : 0;
   s.copy = one_stream ? compute : copy;
   s.compute = compute;
   s.ip = ip;
@@ -1409,7 +1445,7 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
   st.request_id = request_id;
   st.n_hit_chunks = n_hit;
   st.window_chunks = c->W;  // 0: whole-plan mode
-  st.install_batch = s.batch;
+  st.install_batch = s.batch_direct ? s.batch_direct : s.batch;
   st.slot_bytes = c->geo.slot_bytes;
   st.staging_required_bytes = need;
   st.aux_device_bytes = c->aux_bytes;
@@ -1605,7 +1641,21 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
     const int64_t need_seq = s.one_stream ? -1 : s.slot_free_seq[slot];
     uint8_t* dst = s.staging + static_cast<uint64_t>(slot) * c->geo.slot_bytes;
     hipError_t e = hipSuccess;
-    if (!from_file && src_block) {
+    // chunks that the install reads itself and chunks that go through the
+    // ring never share a launch
+    const bool direct = s.batch_direct && !from_file && src_block;
+    if (direct == s.pend_src.empty() && !batch.empty())
+      if ((rc = flush_all())) return rc;
+    if (direct) {
+      const Store& sto = c->store;
+      if (src_block < sto.arena || c->geo.slot_bytes > sto.arena_bytes ||
+          static_cast<uint64_t>(src_block - sto.arena) > sto.arena_bytes - c->geo.slot_bytes) {
+        if ((rc = flush_all())) return rc;
+        fail_with(BSR_E_TRANSFER, "chunk %u: source outside the store arena", i);
+        return host_fail(c, s, BSR_FAIL_TRANSFER, i, all_mask, BSR_E_TRANSFER);
+      }
+      s.pend_src.push_back(sto.arena_dev + (src_block - sto.arena));
+    } else if (!from_file && src_block) {
       // pinned, one block: extend the last run, or start a new one beside it
       const int64_t need = need_seq > s.copy_waited_seq ? need_seq : -1;  // -1: nothing left to wait for
       if (n_runs && need > runs_need)
@@ -1664,11 +1714,12 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
     batch.push_back(i);
     s.pend_tags.push_back(tg);
     ++s.st.n_chunks_enqueued;
-    if (batch.size() == s.batch)
+    if (batch.size() == (direct ? s.batch_direct : s.batch))
       if ((rc = flush_all())) return rc;
   }
   if (hipError_t e = issue_runs(&done)) return fail_runs(e, done);  // nothing of this call stays unstaged
-  if (first_chunk + n_chunks == s.n_hit)
+  const bool enough = !c->cfg.install_batch && s.pend_src.size() * c->geo.slot_bytes >= kDirectFlushBytes;
+  if (first_chunk + n_chunks == s.n_hit || enough)
     if ((rc = flush_batch(c, s))) return launch_failed(c, s, rc);  // the prefix is complete
   s.next_chunk = first_chunk + n_chunks;
   ++s.st.n_windows;

@@ -198,3 +198,74 @@ def test_runs_of_a_scattered_store(record, C, W, flags):
         _check(wi, case, res, gc.restore(5, n), gc.dev.pools, gc.dev.valid)
     finally:
         gc.close()
+
+
+def _direct_workload(groups, C, n_chunks, W):
+    specs = tuple(GroupSpec(f"g{i}", bt, nt, rb, kind="planar" if sp else "contig", split_bytes=sp,
+                            value_kind="bytes") for i, (bt, nt, rb, sp) in enumerate(groups))
+    return Workload(index=500, name="direct", n_tokens=n_chunks * C + 1, chunk_tokens=C, groups=specs,
+                    windows=(W,), pool_factor=2)
+
+
+# one piece; a piece and one vector more; more pieces than workgroups; records
+# and blocks that leave nothing 16-byte aligned, in pieces of up to 8 KiB and
+# planar ones of more than the 8 KiB in flight; planar pieces through the LDS
+# one after the other in a workgroup
+DIRECT = [([(16, 1, 16, 0)], 16, 1, 1), ([(64, 1, 132, 0)], 64, 33, 2), ([(64, 9, 1152, 0)], 64, 40, 32),
+          ([(5, 4, 1148, 0), (7, 8, 140, 132)], 48, 34, 3), ([(128, 2, 132, 124), (64, 1, 2044, 0)], 128, 5, 0),
+          ([(128, 40, 132, 128), (16, 1, 48, 0)], 256, 9, 8)]
+
+
+@pytest.mark.parametrize("groups,C,n_chunks,W", DIRECT)
+@pytest.mark.parametrize("bad", [None, "first", "last"])
+def test_install_straight_from_pinned_memory(groups, C, n_chunks, W, bad):
+    """A small request's chunks go from the pinned store to their blocks with
+    no staging copy; a corrupt word in the first or last chunk is found by the
+    launch that holds it, as in the oracle."""
+    w = _direct_workload(groups, C, n_chunks, W)
+    wi = generate(w)
+    k, g = (0 if bad == "first" else n_chunks - 1), len(groups) - 1
+    case = build_case(wi)
+    n, _, keys = oracle.probe(case.store, wi.tokens, C, wi.salt)
+    byte = case.layout.payload_bytes(g) - 3
+    if bad:
+        case.store.corrupt(keys[k], g, byte, 0x81)
+    res = oracle.windowed_restore(case.layout, case.store, keys, n, W, wi.block_tables, case.pools, case.valid)
+    say(f"case: direct install, {groups}, C={C}, {n_chunks} chunks, W={W}, corrupt {bad}")
+    gc = GpuCase(wi, W=W)
+    try:
+        assert gc.probe(6)[0] == n == n_chunks
+        if bad:
+            gc.corrupt(int(keys[k]), g, byte, 0x81)
+        out = gc.restore(6, n)
+        assert out.stats["n_stage_launches"] == 0
+        assert out.status["fail"] == (bsr.BSR_FAIL_CORRUPT if bad else 0) and out.fallback == res.fallback
+        assert out.status["first_failed_chunk"] == res.first_failed_chunk
+        assert out.status["q"][:len(groups)] == res.q
+        if not bad:
+            _check(wi, case, res, out, gc.dev.pools, gc.dev.valid)
+            return
+        bsr.bsr_request_end(gc.ctx, 6)
+        gc.corrupt(int(keys[k]), g, byte, 0x81)  # put back: the shared words were left as a launch needs them
+        assert gc.probe(7)[0] == n and gc.restore(7, n).exposed_tokens == n * C
+    finally:
+        gc.close()
+
+
+def test_direct_and_staged_chunks_in_one_request(tmp_path):
+    """Runs of chunks from the pinned store and from files alternate: the
+    former are installed straight from there, the latter through the ring."""
+    w = _direct_workload([(16, 3, 132, 0), (32, 2, 132, 128)], 32, 40, 6)
+    wi = generate(w)
+    case, n, res = _oracle(wi, 6)
+    pinned = [i for i in range(40) if (i // 3) % 2 or i > 33]
+    say("case: 40 chunks, three pinned, three in files, and so on, W=6")
+    gc = GpuCase(wi, W=6, pinned_chunks=pinned)
+    try:
+        gc.put_files(str(tmp_path), [i for i in range(40) if i not in pinned])
+        assert gc.probe(8)[0] == n == 40
+        out = gc.restore(8, n)
+        _check(wi, case, res, out, gc.dev.pools, gc.dev.valid)
+        assert out.stats["file_tier_chunks"] == 40 - len(pinned) == out.stats["n_stage_launches"]
+    finally:
+        gc.close()
