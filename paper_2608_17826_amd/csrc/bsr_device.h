@@ -291,7 +291,19 @@ struct FinishParams {
   uint32_t total_blocks;    // sum of n_req_blocks
   uint32_t chunk_tokens;
   uint64_t exposed_if_valid;
+  bsr_dev_status* mirror;   // commit: the status block is also written here (pinned host memory); may be null
   GroupValid g[BSR_MAX_GROUPS];
+};
+
+// Block tables into pinned host memory: the groups' first n entries one after
+// the other to `out`, then `ticket` to *flag.
+struct TablesParams {
+  uint32_t n_groups;
+  uint32_t ticket;
+  int32_t* out;
+  uint32_t* flag;
+  const int32_t* table[BSR_MAX_GROUPS];
+  uint32_t n[BSR_MAX_GROUPS];
 };
 
 // Staging copy (pinned host memory -> ring slots) done by a kernel on the
@@ -370,5 +382,6 @@ hipError_t launch_verify(const VerifyParams& p, hipStream_t s);
 hipError_t launch_stage(const StageRun* runs, uint32_t n_runs, hipStream_t s, hipEvent_t start = nullptr,
                         hipEvent_t stop = nullptr);
 hipError_t launch_finish(const FinishParams& p, hipStream_t s);
+hipError_t launch_tables(const TablesParams& p, hipStream_t s);
 
 }  // namespace bsr

@@ -82,6 +82,12 @@ constexpr uint64_t kDirectFlushBytes = 1ull << 20;
 // chunks (230 MB) gain nothing and 7 chunks lose 0.4.  The gain starts
 // where a launch outgrows the 256 MiB Infinity Cache in front of HBM.
 constexpr uint64_t kSerpentineBytes = 256ull << 20;
+// Block table entries that one bind reads back through a session slot's
+// landing zone (64 KiB); larger tables are copied, 16-20 us a group.
+constexpr uint64_t kTableEntries = 16384;
+constexpr uint64_t kTablesOffset = 256;  // behind the status mirror
+constexpr uint64_t kHostBytes = kTablesOffset + (kTableEntries + 1) * sizeof(int32_t);
+constexpr uint64_t kSpinNs = 100000;  // a bind polls this long before it waits for its stream
 constexpr uint32_t kTimingFlags = BSR_FLAG_TIME_INSTALL | BSR_FLAG_TIME_STAGE;
 constexpr uint64_t kArenaBlockAlign = 4096;
 uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
@@ -363,6 +369,14 @@ struct SessionRes {
   TagPair* partials = nullptr;            // per-wave tag partials of one install launch
   bsr::VerifyAux* verify_aux = nullptr;   // verify words
   bsr_dev_status* host_status = nullptr;  // pinned mirror of the status block
+  bsr_dev_status* mirror_dev = nullptr;   // the device's view of it; null: read back by a copy
+  // Pinned landing zone of one bind's block tables (kTableEntries ids, then
+  // the flag), in the same allocation; null: tables are copied back.  A bind
+  // takes any slot's free zone, and `tables_busy` while it does.
+  int32_t* tables = nullptr;
+  int32_t* tables_dev = nullptr;
+  uint32_t table_ticket = 0;
+  bool tables_busy = false;
   std::vector<hipEvent_t> full_ev, free_ev;
   bool in_use = false;
   // A context that allocates nothing: partials and verify words are in the
@@ -663,6 +677,7 @@ int enqueue_finish(bsr_ctx* c, Session& s, uint32_t mode, uint32_t reason, uint3
   fp.reason = reason;
   fp.chunk = chunk;
   fp.group_mask = mask;
+  fp.mirror = mode == bsr::kFinishCommit ? c->res[s.res].mirror_dev : nullptr;
   return hip_check(bsr::launch_finish(fp, s.compute), "finish launch");
 }
 
@@ -931,7 +946,16 @@ static int ctx_create(const bsr_layout* layout, const bsr_config* config, bsr_ct
       } else {
         ok = ok && hipMalloc(reinterpret_cast<void**>(&r.partials), c->partials_bytes) == hipSuccess &&
              hipMalloc(reinterpret_cast<void**>(&r.verify_aux), sizeof(bsr::VerifyAux)) == hipSuccess &&
-             hipHostMalloc(reinterpret_cast<void**>(&r.host_status), sizeof(bsr_dev_status), hipHostMallocDefault) == hipSuccess;
+             hipHostMalloc(reinterpret_cast<void**>(&r.host_status), kHostBytes, hipHostMallocDefault) == hipSuccess;
+        void* dv = nullptr;
+        if (ok && hipHostGetDevicePointer(&dv, r.host_status, 0) == hipSuccess && dv) {
+          r.mirror_dev = static_cast<bsr_dev_status*>(dv);
+          r.tables = reinterpret_cast<int32_t*>(reinterpret_cast<uint8_t*>(r.host_status) + kTablesOffset);
+          r.tables_dev = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(dv) + kTablesOffset);
+          r.tables[kTableEntries] = 0;  // the flag: no ticket yet
+        } else {
+          (void)hipGetLastError();
+        }
       }
       for (uint32_t i = 0; ok && i < E; ++i)
         ok = hipEventCreateWithFlags(&r.full_ev[i], hipEventDisableTiming) == hipSuccess &&
@@ -1242,6 +1266,79 @@ int bsr_probe(bsr_ctx* c, uint64_t request_id, uint64_t salt, const int32_t* tok
 
 // ---- bind ----------------------------------------------------------------------
 
+// A block table's advertised part: every id inside the pool, none twice.
+static int check_table(uint32_t g, const int32_t* bt, uint32_t n, uint32_t pool_blocks, std::vector<uint8_t>& seen) {
+  seen.assign(pool_blocks, 0);
+  for (uint32_t k = 0; k < n; ++k) {
+    const int32_t b = bt[k];
+    if (b < 0 || static_cast<uint32_t>(b) >= pool_blocks)
+      return fail_with(BSR_E_ARG, "group %u: block_table[%u] = %d outside [0, %u)", g, k, b, pool_blocks);
+    if (seen[b]++) return fail_with(BSR_E_ARG, "group %u: block %d appears twice in the prefix", g, b);
+  }
+  return BSR_OK;
+}
+
+// Read the advertised part of every group's block table back once and check
+// it, behind what the compute stream holds.  The context lock is not held
+// while the device is waited for.
+static int check_tables(bsr_ctx* c, const FinishParams& fp, uint64_t total, hipStream_t compute) {
+  if (total == 0) return BSR_OK;
+  std::vector<uint8_t> seen;
+  SessionRes* zone = nullptr;
+  if (total <= kTableEntries) {
+    std::lock_guard<std::mutex> lk(c->mu);
+    for (SessionRes& r : c->res)
+      if (r.tables && !r.tables_busy) {
+        r.tables_busy = true;
+        zone = &r;
+        break;
+      }
+  }
+  if (!zone) {  // one copy per group
+    std::vector<int32_t> bt;
+    for (uint32_t g = 0; g < fp.n_groups; ++g) {
+      const uint32_t n = fp.g[g].n_req_blocks;
+      bt.resize(n);
+      int rc = hip_check(hipMemcpyAsync(bt.data(), fp.g[g].block_table, n * sizeof(int32_t), hipMemcpyDeviceToHost, compute), "block table readback");
+      if (!rc) rc = hip_check(hipStreamSynchronize(compute), "hipStreamSynchronize");
+      if (!rc) rc = check_table(g, bt.data(), n, fp.g[g].pool_blocks, seen);
+      if (rc) return rc;
+    }
+    return BSR_OK;
+  }
+  uint32_t* flag = reinterpret_cast<uint32_t*>(zone->tables + kTableEntries);
+  bsr::TablesParams p{};
+  p.n_groups = fp.n_groups;
+  p.ticket = ++zone->table_ticket;
+  p.out = zone->tables_dev;
+  p.flag = reinterpret_cast<uint32_t*>(zone->tables_dev + kTableEntries);
+  for (uint32_t g = 0; g < fp.n_groups; ++g) {
+    p.table[g] = fp.g[g].block_table;
+    p.n[g] = fp.g[g].n_req_blocks;
+  }
+  int rc = hip_check(bsr::launch_tables(p, compute), "block table readback");
+  if (!rc) {
+    const uint64_t until = now_ns() + kSpinNs;
+    while (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != p.ticket && now_ns() < until) {
+    }
+    if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != p.ticket) {
+      // the stream holds other work, or has failed; a zone whose kernel may
+      // still be to come stays taken
+      rc = hip_check(hipStreamSynchronize(compute), "hipStreamSynchronize");
+      if (rc) return rc;
+      if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != p.ticket) return fail_with(BSR_E_TRANSFER, "block table readback did not run");
+    }
+    const int32_t* bt = zone->tables;
+    for (uint32_t g = 0; !rc && g < fp.n_groups; ++g) {
+      rc = check_table(g, bt, p.n[g], fp.g[g].pool_blocks, seen);
+      bt += p.n[g];
+    }
+  }
+  std::lock_guard<std::mutex> lk(c->mu);
+  zone->tables_busy = false;
+  return rc;
+}
+
 int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_group_dst* dst,
                      void* staging, uint64_t staging_bytes, bsr_dev_status* status, void* copy_stream,
                      void* compute_stream) {
@@ -1287,7 +1384,6 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
   ip.h.xcd_log2 = c->xcd_log2;
   ip.h.status = status;
   uint32_t total = 0;
-  std::vector<int32_t> bt;
   for (uint32_t g = 0; g < G; ++g) {
     const bsr_group_dst& d = dst[g];
     const uint32_t B = c->geo.L.groups[g].block_tokens;
@@ -1295,22 +1391,6 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
     if (!d.block_table || !d.tensor_bases || !d.valid) return fail_with(BSR_E_ARG, "group %u: NULL destination pointer", g);
     if (d.n_blocks < nreq) return fail_with(BSR_E_ARG, "group %u: block table has %u blocks, prefix needs %llu", g, d.n_blocks, (unsigned long long)nreq);
     if (d.pool_blocks == 0) return fail_with(BSR_E_ARG, "group %u: pool_blocks is 0", g);
-    if (!trusted) {
-      // copy the advertised part of the block table back once and check it
-      bt.resize(nreq);
-      if (nreq) {
-        int rc = hip_check(hipMemcpyAsync(bt.data(), d.block_table, nreq * 4, hipMemcpyDeviceToHost, compute), "block table readback");
-        if (!rc) rc = hip_check(hipStreamSynchronize(compute), "hipStreamSynchronize");
-        if (rc) return rc;
-      }
-      std::vector<uint8_t> seen(d.pool_blocks, 0);
-      for (uint64_t k = 0; k < nreq; ++k) {
-        const int32_t b = bt[k];
-        if (b < 0 || static_cast<uint32_t>(b) >= d.pool_blocks)
-          return fail_with(BSR_E_ARG, "group %u: block_table[%llu] = %d outside [0, %u)", g, (unsigned long long)k, b, d.pool_blocks);
-        if (seen[b]++) return fail_with(BSR_E_ARG, "group %u: block %d appears twice in the prefix", g, b);
-      }
-    }
     // the group's record sits at its dispatch position
     uint32_t pos = 0;
     while (c->geo.order[pos] != g) ++pos;
@@ -1345,6 +1425,8 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
     total += static_cast<uint32_t>(nreq);
   }
   fp.total_blocks = total;
+  if (!trusted)
+    if (int rc = check_tables(c, fp, total, compute)) return rc;
 
   std::lock_guard<std::mutex> lk(c->mu);
   if (c->bound.count(request_id)) return fail_with(BSR_E_STATE, "request %llu is already bound", (unsigned long long)request_id);
@@ -1785,7 +1867,8 @@ static int complete_session(bsr_ctx* c, Session& s, std::unique_lock<std::mutex>
     if (!rc) rc = enqueue_finish(c, s, bsr::kFinishCommit, 0, BSR_NO_CHUNK, 0);
   }
   if (!rc) rc = flush_batch(c, s);
-  if (!rc) rc = hip_check(hipMemcpyAsync(res.host_status, s.status, sizeof(bsr_dev_status), hipMemcpyDeviceToHost, s.compute), "status readback");
+  if (!rc && !(run_commit && res.mirror_dev))  // else the commit kernel has written the mirror
+    rc = hip_check(hipMemcpyAsync(res.host_status, s.status, sizeof(bsr_dev_status), hipMemcpyDeviceToHost, s.compute), "status readback");
   s.completing = true;
   const hipStream_t compute = s.compute, copy = s.copy;
   // Once the compute stream has waited for the last copy event, every copy

@@ -269,3 +269,36 @@ def test_direct_and_staged_chunks_in_one_request(tmp_path):
         assert out.stats["file_tier_chunks"] == 40 - len(pinned) == out.stats["n_stage_launches"]
     finally:
         gc.close()
+
+
+@pytest.mark.parametrize("n_chunks", [1, 64, 1024, 1025])
+def test_bind_checks_the_last_block_id(n_chunks):
+    """Block tables of 16 to 16,400 entries over two groups, read back in one
+    launch up to 16,384 and by copies beyond: an id past the pool or a
+    repeated one in the very last entry is refused, with the valid bytes as
+    they were, and the same tables put right restore the oracle's image."""
+    w = Workload(index=600, name="tables", n_tokens=n_chunks * 16, chunk_tokens=16,
+                 groups=(GroupSpec("a", 16, 1, 8, value_kind="bytes"), GroupSpec("b", 1, 1, 4, value_kind="bytes"))
+                 if n_chunks < 1024 else (GroupSpec("b", 1, 1, 4, value_kind="bytes"),),
+                 windows=(32,), pool_factor=2)
+    wi = generate(w)
+    case, n, res = _oracle(wi, 32)
+    gc = GpuCase(wi, W=32)
+    try:
+        say(f"case: {sum(len(t) for t in wi.block_tables)} block table entries")
+        assert gc.probe(9)[0] == n == n_chunks
+        table, good = gc.dev.block_tables[-1], int(wi.block_tables[-1][-1])
+        for bad, word in ((wi.pool_blocks[-1], "outside"), (-1, "outside"), (int(wi.block_tables[-1][0]), "twice")):
+            table[-1] = bad
+            torch.cuda.synchronize()
+            with pytest.raises(bsr.BsrError) as e:
+                gc.session.bind(9, n, gc.dsts())
+            assert e.value.code == bsr.BSR_E_ARG and word in str(e.value)
+            np.testing.assert_array_equal(gc.valid_host(len(w.groups) - 1), wi.valid_init[-1])
+        table[-1] = good
+        torch.cuda.synchronize()
+        with torch.cuda.stream(gc.session.compute_stream):
+            torch.cuda._sleep(2_000_000)  # the readback then waits for the stream, past its polling
+        _check(wi, case, res, gc.restore(9, n), gc.dev.pools, gc.dev.valid)
+    finally:
+        gc.close()
