@@ -113,14 +113,19 @@ extern "C" {
                                       order, not events between the two streams, orders its copies,
                                       installs and slot reuse; its chunks in a pinned arena are installed
                                       straight from there, with no staging copy (each still counts as one
-                                      live slot of the ring, which is provided as for any request) */
+                                      live slot of the ring, which is provided as for any request).  So is
+                                      a request of at most 768 MiB, all of it in a pinned arena, of a context
+                                      without a staging budget, and any chunk in a pinned arena while more
+                                      than one request is bound */
 #define BSR_FLAG_SDMA_COPIES 4u   /* stage chunks with the copy engine (hipMemcpyAsync) instead of the
                                       library's staging-copy kernel.  By default a small kernel on the copy
                                       stream reads each run of chunks from pinned host memory (the library's
                                       arena, an adopted arena that HIP reports pinned over its whole range,
                                       or the file tier's bounce buffers) into the ring; a source HIP does not
                                       report pinned is always copied by the copy engine, and so is every run
-                                      staged on a copy stream while more than one request is bound */
+                                      staged on a copy stream while more than one request is bound.  Chunks
+                                      installed straight from a pinned arena (see BSR_FLAG_TWO_STREAMS) are
+                                      not staged at all */
 
 /* fault injection (bsr_debug_inject), forced from the host */
 #define BSR_INJECT_NONE 0
@@ -457,8 +462,8 @@ int bsr_request_bind(bsr_ctx* ctx, uint64_t request_id, uint32_t n_hit_chunks,
  * yet requested).  Asynchronous: for each chunk it looks the entries up
  * (a missing entry, an injected delay beyond the window deadline, or a
  * failed copy submission fails the window), waits for the chunk's slot to be
- * released, and enqueues the pinned-host -> slot copy on copy_stream (a small
- * request's install reads pinned memory itself, see BSR_FLAG_TWO_STREAMS); per
+ * released, and enqueues the pinned-host -> slot copy on copy_stream (some
+ * requests' installs read pinned memory themselves, see BSR_FLAG_TWO_STREAMS); per
  * install batch (which may span windows: chunks left over at the end of a
  * call join the next call's batch, and every later call of the request --
  * commit, invalidate, mark, end -- installs them first) it enqueues the

@@ -66,9 +66,21 @@ uint64_t now_ns() {
 
 constexpr uint64_t kAlign = 256;
 // Requests of at most this many chunk bytes stay on the compute stream
-// (Session::one_stream): staged there, or, from pinned memory, installed with
-// no staging copy at all.
+// (Session::one_stream), staged there when they cannot be installed straight
+// from pinned memory.
 constexpr uint64_t kOneStreamBytes = 64ull << 20;
+// Requests of at most this many chunk bytes, all of them in the pinned store,
+// are installed straight from there on the compute stream when no other
+// request can be bound beside them (no staging budget): the link is loaded from
+// the first chunk to the last, where the ring's pipeline has its first copy and
+// its last install to itself, hands over between two streams at every batch and
+// loses link rate to the installs beside its copies.  Measured in turn, ring
+// and direct: 75 MB of 2.4 MB chunks at W = 8 1,516 and 1,396 us, 155 MB of
+// 607 KB chunks 2,992 and 2,856, 525 MB of 16.4 MB chunks 9,365 and 9,268,
+// 621 MB of 9.7 MB chunks 11,174 and 11,069, 3.15 GB 55.56 and 55.42 ms: the
+// gain, about 100 us a request, is 1% at this line and less beyond, where a
+// staging copy also keeps to 24 CUs for the seconds that it may take.
+constexpr uint64_t kDirectBytes = 768ull << 20;
 // Chunks that the install reads straight from pinned memory are launched at
 // the end of a window once they hold this many bytes, or else join the next
 // window's: a launch costs about 15 us beside its 18 us/MiB of link time.  The
@@ -401,8 +413,8 @@ struct Session {  // one bound request
   bool one_stream = false;
   uint32_t batch = 0;       // chunks per install launch
   // Chunks per install launch that reads pinned memory itself (requests on
-  // one stream, where a staging copy could not overlap an install anyway);
-  // 0: every chunk goes through the ring.
+  // one stream, and any request while it shares the link); 0: every chunk goes
+  // through the ring.
   uint32_t batch_direct = 0;
   bool copy_dirty = false;  // the copy stream holds work no compute-stream wait covers yet
   uint32_t time_flags = 0;  // BSR_FLAG_TIME_INSTALL / BSR_FLAG_TIME_STAGE, taken at bind
@@ -527,10 +539,10 @@ hipError_t stage_copy(bsr_ctx* c, Session& s, const Run* runs, uint32_t n, const
                       uint64_t extent, uint32_t* done) {
   *done = 0;
   s.copy_dirty = true;
-  // With several requests bound, each staging on a copy stream of its own,
-  // their k_stage launches would run side by side on the link; the copy
-  // engine queues them instead (3 requests of 512K tokens: 56.9 against
-  // 56.6 GB/s in aggregate, the installs beside them at 76% of HBM against 67%).
+  // With several requests bound, each staging on a copy stream of its own
+  // (BSR_FLAG_TWO_STREAMS, or chunks of the file tier), their k_stage launches
+  // would run side by side on the link; the copy engine queues them instead
+  // (3 requests of 512K tokens at W = 32: 56.9 against 56.6 GB/s in aggregate).
   const bool shared_link = c->bound.size() > 1 && s.copy != s.compute;
   if (!c->kernel_copies || shared_link || !dev || !base) {
     for (; *done < n; ++*done) {
@@ -588,12 +600,16 @@ int flush_batch(bsr_ctx* c, Session& s) {
     return fail_with(BSR_E_TRANSFER, "injected install launch failure (batch with chunk %u)", at);
   }
   SessionRes& r = c->res[s.res];
+  const bool direct = !s.pend_src.empty();
+  // On one stream the copies already precede this install; a direct launch has
+  // no copies and uses no slot, so it leaves the slots' release events alone.
+  const bool events = !s.one_stream && !direct;
   const uint32_t E = static_cast<uint32_t>(r.full_ev.size());
-  const int64_t seq = s.batch_seq++;
-  hipEvent_t full = r.full_ev[seq % E];
-  hipEvent_t freed = r.free_ev[seq % E];
+  const int64_t seq = direct ? -1 : s.batch_seq++;
+  hipEvent_t full = events ? r.full_ev[seq % E] : nullptr;
+  hipEvent_t freed = events ? r.free_ev[seq % E] : nullptr;
   int rc;
-  if (!s.one_stream) {  // on one stream the copies already precede this install
+  if (events) {
     if ((rc = hip_check(hipEventRecord(full, s.copy), "hipEventRecord(full)"))) return rc;
     if ((rc = hip_check(hipStreamWaitEvent(s.compute, full, 0), "hipStreamWaitEvent(full)"))) return rc;
     s.copy_dirty = false;
@@ -602,7 +618,6 @@ int flush_batch(bsr_ctx* c, Session& s) {
   // the kernel takes chunk first_chunk + c to slot first_slot + c, less W
   // once: a launch holds consecutive chunks, at most W of them
   // (a direct launch uses no slot, so only the run matters)
-  const bool direct = !s.pend_src.empty();
   if ((!direct && chunks.size() > s.window) || chunks.back() - chunks.front() + 1 != chunks.size() ||
       (direct && s.pend_src.size() != chunks.size()))
     return fail_with(BSR_E_STATE, "install batch of %zu chunks is not a run of at most W = %u", chunks.size(), s.window);
@@ -645,8 +660,9 @@ int flush_batch(bsr_ctx* c, Session& s) {
   // kernel reads only the tag partials, which the next install (later on
   // this stream) overwrites after it.  Releasing here keeps the verify off
   // the copy engine's path to the slots.
-  if (!s.one_stream && (rc = hip_check(hipEventRecord(freed, s.compute), "hipEventRecord(free)"))) return rc;
-  for (uint32_t ch : chunks) s.slot_free_seq[ch % s.window] = seq;
+  if (events && (rc = hip_check(hipEventRecord(freed, s.compute), "hipEventRecord(free)"))) return rc;
+  if (!direct)
+    for (uint32_t ch : chunks) s.slot_free_seq[ch % s.window] = seq;
   if (!direct) {  // a direct launch has checked its tags itself
     VerifyParams vp{};
     vp.partials = r.partials;
@@ -845,10 +861,10 @@ static int ctx_create(const bsr_layout* layout, const bsr_config* config, bsr_ct
   c->batch_one = config->install_batch ? b : std::min(W ? W : 32u, static_cast<uint32_t>(BSR_MAX_INSTALL_BATCH));
   while (c->batch_one > b && static_cast<uint64_t>(c->batch_one) * c->geo.wg_per_chunk * bsr::kInstallThreads >= (1ull << 32))
     --c->batch_one;
-  // a direct launch holds no ring slot, so W does not bound it; a request on
-  // one stream has at most kOneStreamBytes of chunks to put into it
+  // a direct launch holds no ring slot, so W does not bound it; a request has
+  // at most kDirectBytes of chunks to put into it
   c->batch_direct = config->install_batch ? b : static_cast<uint32_t>(std::min<uint64_t>(
-      BSR_MAX_INSTALL_BATCH, std::max<uint64_t>(1, kOneStreamBytes / c->geo.slot_bytes)));
+      BSR_MAX_INSTALL_BATCH, std::max<uint64_t>(1, kDirectBytes / c->geo.slot_bytes)));
   c->device = config->hip_device;
   c->budget = B;
   c->store.index.resize(layout->n_groups);
@@ -1485,9 +1501,17 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
   // A request of at most kOneStreamBytes of chunks is staged on the compute
   // stream: its copies and installs are short, and the hand-over between two
   // streams (an event recorded on one, waited for on the other) costs about
-  // as much as they do.
-  const bool one_stream = !(c->cfg.flags & BSR_FLAG_TWO_STREAMS) &&
-                          static_cast<uint64_t>(n_hit) * c->geo.slot_bytes <= kOneStreamBytes;
+  // as much as they do.  One that needs no staging stays there up to
+  // kDirectBytes; chunks of the file tier go through the ring, and their
+  // copies need a stream beside the installs.  A larger request, or one under a
+  // staging budget, is installed straight from pinned memory while it shares
+  // the link (bsr_restore_window).
+  const bool two_streams = (c->cfg.flags & BSR_FLAG_TWO_STREAMS) != 0;
+  const bool can_direct = !two_streams && c->kernel_copies && c->store.arena_dev;
+  const bool all_direct = can_direct && c->res.size() == 1 &&
+                          std::all_of(rq.tier.begin(), rq.tier.begin() + n_hit, [](uint8_t t) { return t == kTierPinned; });
+  const bool one_stream = !two_streams && static_cast<uint64_t>(n_hit) * c->geo.slot_bytes <=
+                                              (all_direct ? kDirectBytes : kOneStreamBytes);
   // no copy of this request may overwrite the ring before earlier compute work is done
   if (!one_stream) {
     if (int rc = hip_check(hipEventRecord(res.free_ev[0], compute), "hipEventRecord")) return rc;
@@ -1505,7 +1529,7 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
   s.one_stream = one_stream;
   s.time_flags = c->cfg.flags & kTimingFlags;
   s.batch = one_stream ? c->batch_one : c->batch;
-  s.batch_direct = one_stream && c->kernel_copies && c->store.arena_dev ? c->batch_direct : 0;
+  s.batch_direct = can_direct ? c->batch_direct : 0;
   s.copy = one_stream ? compute : copy;
   s.compute = compute;
   s.ip = ip;
@@ -1527,7 +1551,7 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
   st.request_id = request_id;
   st.n_hit_chunks = n_hit;
   st.window_chunks = c->W;  // 0: whole-plan mode
-  st.install_batch = s.batch_direct ? s.batch_direct : s.batch;
+  st.install_batch = one_stream && s.batch_direct ? s.batch_direct : c->res.size() > 1 ? std::max(s.batch, s.batch_direct) : s.batch;
   st.slot_bytes = c->geo.slot_bytes;
   st.staging_required_bytes = need;
   st.aux_device_bytes = c->aux_bytes;
@@ -1725,7 +1749,10 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
     hipError_t e = hipSuccess;
     // chunks that the install reads itself and chunks that go through the
     // ring never share a launch
-    const bool direct = s.batch_direct && !from_file && src_block;
+    // Sharing the link, a request is installed straight from pinned memory
+    // whatever its size: two requests of 310 MB, W = 8, take 14.2 ms through
+    // the copy engine and 11.0 so (44 and 56 GB/s in aggregate).
+    const bool direct = s.batch_direct && !from_file && src_block && (s.one_stream || c->bound.size() > 1);
     if (direct == s.pend_src.empty() && !batch.empty())
       if ((rc = flush_all())) return rc;
     if (direct) {

@@ -264,6 +264,49 @@ def test_staging_path_changes_mid_request():
         bsr.bsr_ctx_destroy(ctx)
 
 
+@pytest.mark.parametrize("bad", [None, ("x", 2), ("x", 4), ("y", 2)])
+def test_ring_and_direct_installs_alternate_while_requests_come_and_go(bad):
+    """A request alternates between the ring (alone) and installs straight
+    from pinned memory (beside another request), several times over a ring of
+    W = 3 slots, so that slots are reused across the changes; a corrupt chunk,
+    met by either kind of launch, fails its own request alone."""
+    W = 3
+    xi = _variant(2, 2, n_tokens=40 * 256)
+    yis = [_variant(2, 102 + 100 * j, n_tokens=4 * 256) for j in range(4)]
+    ctx, slot = _ctx([xi, *yis], W, budget=2 * W * 9_707_520)
+    try:
+        def corrupt(case, keys):
+            case.store.corrupt(keys[bad[1]], 1, 1001, 0x5A)
+        x = Tenant(ctx, xi, 90, W, mutate=corrupt if bad and bad[0] == "x" else None)
+        ys = [Tenant(ctx, yi, 91 + j, W, mutate=corrupt if bad and bad[0] == "y" and j == 1 else None)
+              for j, yi in enumerate(yis)]
+        faulty = None if not bad else x if bad[0] == "x" else ys[1]
+        say(f"case: 40 chunks, W=3, beside four requests of 4 chunks, one after the other, corrupt: {bad}")
+        log = []
+        for t in (x, *ys):
+            t.probe()
+        if faulty:
+            addr, _, _ = bsr.bsr_store_payload(ctx, int(faulty.keys[bad[1]]), 1)
+            ctypes.c_uint8.from_address(addr + 1001).value ^= 0x5A
+        assert _bind(x, log)
+        assert x.step()                       # chunks 0-2 alone: the ring
+        for y in ys:
+            assert _bind(y, log)
+            assert x.step() and y.step() and x.step()
+            while y.step():
+                pass
+            y.commit()
+            assert x.step()
+        while x.step():
+            pass
+        x.commit()
+        for t in (x, *ys):
+            t.check_failure(bsr.BSR_FAIL_CORRUPT) if t is faulty else t.check_success()
+        assert 0 < x.out.stats["stage_bytes"] < x.out.stats["h2d_bytes"]
+    finally:
+        bsr.bsr_ctx_destroy(ctx)
+
+
 def test_budget_zero_keeps_the_lock_and_slot_count_limits():
     W = 2
     wis = [_variant(1, 1 + 100 * j) for j in range(3)]

@@ -271,6 +271,28 @@ def test_direct_and_staged_chunks_in_one_request(tmp_path):
         gc.close()
 
 
+@pytest.mark.parametrize("n_chunks,in_file,staged", [(64, 0, 0), (65, 0, 0), (65, 1, 65), (65, 64, 65)])
+def test_requests_beyond_64_mib(tmp_path, n_chunks, in_file, staged):
+    """Chunks of 1 MiB.  A request of more than 64 of them is installed
+    straight from pinned memory if all are there; with any in a file its
+    chunks go through the ring, on two streams."""
+    w = _direct_workload([(64, 4, 1024, 0)], 256, n_chunks, 8)
+    wi = generate(w)
+    case, n, res = _oracle(wi, 8)
+    say(f"case: {n_chunks} chunks of 1 MiB, the last {in_file} in files, W=8")
+    first_file = n_chunks - in_file
+    gc = GpuCase(wi, W=8, pinned_chunks=range(first_file))
+    try:
+        if in_file:
+            gc.put_files(str(tmp_path), range(first_file, n_chunks))
+        assert gc.probe(8)[0] == n == n_chunks
+        out = gc.restore(8, n)
+        _check(wi, case, res, out, gc.dev.pools, gc.dev.valid)
+        assert out.stats["file_tier_chunks"] == in_file and out.stats["stage_bytes"] == staged << 20
+    finally:
+        gc.close()
+
+
 @pytest.mark.parametrize("n_chunks", [1, 64, 1024, 1025])
 def test_bind_checks_the_last_block_id(n_chunks):
     """Block tables of 16 to 16,400 entries over two groups, read back in one
