@@ -87,6 +87,14 @@ constexpr uint64_t kDirectBytes = 768ull << 20;
 // 1K-token workload (295 KB windows) takes 132 us with a launch per window,
 // 111 with 512 KiB, 96 with 1 MiB and 99 in one launch, which starts late.
 constexpr uint64_t kDirectFlushBytes = 1ull << 20;
+// Chunks that hold less than the request has launched so far wait for the next
+// window too, up to this many bytes: the launches of many small windows double
+// in size, each about as long as the device still has work before it, and a
+// caller that pauses between windows leaves at most 1.2 ms of link time to
+// the last of them.  Measured in turn, a launch per window and so: 155 MB in
+// 1.2 MB windows 3,735 and 2,882 us, 295 MB in 4.9 MB windows 6,018 and 5,474,
+// 55 MB in 707 KB windows 1,710 and 1,579, 513 MB in 131 MB windows the same.
+constexpr uint64_t kDirectHoldBytes = 64ull << 20;
 // Install launches whose staged chunks exceed this many bytes walk their
 // chunks in alternate directions from one dispatch position to the next
 // (InstallHead::serpentine).  Measured on the 512K 4-group layout: launches
@@ -416,6 +424,7 @@ struct Session {  // one bound request
   // one stream, and any request while it shares the link); 0: every chunk goes
   // through the ring.
   uint32_t batch_direct = 0;
+  uint64_t direct_bytes = 0;  // launched with no ring in between
   bool copy_dirty = false;  // the copy stream holds work no compute-stream wait covers yet
   uint32_t time_flags = 0;  // BSR_FLAG_TIME_INSTALL / BSR_FLAG_TIME_STAGE, taken at bind
   int host_fail = BSR_FAIL_NONE;
@@ -647,6 +656,7 @@ int flush_batch(bsr_ctx* c, Session& s) {
     dp.aux = r.verify_aux;
     for (size_t i = 0; i < chunks.size(); ++i) std::copy(tags[i].begin(), tags[i].end(), dp.expected[i]);
     launched = bsr::launch_install_direct(dp, s.compute, t0, t1);
+    s.direct_bytes += static_cast<uint64_t>(ip.h.n_chunks) * c->geo.slot_bytes;
   } else {
     launched = bsr::launch_install(ip, ip.h.n_chunks * ip.h.wg_per_chunk, s.compute, t0, t1);
   }
@@ -1827,7 +1837,8 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
       if ((rc = flush_all())) return rc;
   }
   if (hipError_t e = issue_runs(&done)) return fail_runs(e, done);  // nothing of this call stays unstaged
-  const bool enough = !c->cfg.install_batch && s.pend_src.size() * c->geo.slot_bytes >= kDirectFlushBytes;
+  const uint64_t least = std::max(kDirectFlushBytes, std::min(s.direct_bytes, kDirectHoldBytes));
+  const bool enough = !c->cfg.install_batch && s.pend_src.size() * c->geo.slot_bytes >= least;
   if (first_chunk + n_chunks == s.n_hit || enough)
     if ((rc = flush_batch(c, s))) return launch_failed(c, s, rc);  // the prefix is complete
   s.next_chunk = first_chunk + n_chunks;
