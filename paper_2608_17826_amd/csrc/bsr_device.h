@@ -234,21 +234,32 @@ struct DirectParams {
   const uint8_t* src[BSR_MAX_INSTALL_BATCH];
   bsr_dev_status* status;
   VerifyAux* aux;
+  uint32_t stretches;  // set by the launch: each workgroup takes consecutive pieces
+  uint32_t pad;
   uint64_t expected[BSR_MAX_INSTALL_BATCH][BSR_MAX_GROUPS];  // stored tags
 };
-// Its grid: workgroups that take pieces in turn, as many as hold
-// kDirectInflight bytes of loads between them at the launch's average piece,
-// at least kDirectMinGrid and two pieces each, at most kDirectMaxGrid.  The
-// link needs some 200 KB in flight, but a workgroup loads nothing while it
-// decodes and stores, and small pieces keep few bytes in flight each.
-// Measured in us per request on one box (kDirectInflight 256 KiB / 512 KiB /
-// 1 MiB / 2 MiB): 63 MB of 8 KiB pieces 1,227 / 1,199 / 1,185 / 1,192; 20 MB
-// of eight groups' pieces, 1.9 KB on average, 717 / 691 / 639 / 652; one
-// workgroup per piece instead loses link rate at its start (a staging kernel
-// with 8 MB in flight moves 2.3 MB at 40 GB/s, one with 192 KiB at 50).
+// Its grid: workgroups that take pieces in turn, each with two in flight, as
+// many as hold kDirectInflight bytes of loads between them at the launch's
+// average piece, at least kDirectMinGrid, at most kDirectMaxGrid and one for
+// every kDirectMinPieces pieces.  Measured in us per request on one box, by
+// workgroups (621 MB in 8 KiB pieces / 155 MB in launches of 19 MB, 5.8 KB
+// pieces / 55 MB of eight groups' pieces, 1.9 KB on average / 2.4 MB in 6 KiB
+// pieces): 16: 10,988 / 3,010 / 3,287 / 103; 28: 11,997 / 2,890 / 2,350 / 100;
+// 40: 11,311 / 3,098 / 1,995 / 104; 64: 10,997 / 2,860 / 1,678 / 103; 96: 11,017 /
+// 2,842 / 1,594 / 104; 192: 11,079 / 2,840 / 1,496 / 110.  (The link is slower
+// between some 400 and 700 KB in flight than on either side; pieces smaller
+// than 8 KiB need more workgroups than the lower side has.)
 constexpr uint64_t kDirectInflight = 1u << 20;
-constexpr uint64_t kDirectMinGrid = 64;
+constexpr uint64_t kDirectMinGrid = 16;
 constexpr uint64_t kDirectMaxGrid = 512;
+constexpr uint64_t kDirectMinPieces = 8;
+// From this many (workgroup, chunk, group) sums in a launch on, a workgroup
+// takes consecutive pieces, and so few chunks: every sum that is not zero is
+// two atomics at the end.  Eight groups, 32-token chunks, some 270 x 32 x 8
+// sums: 1,287 tokens 146 us in turn and 135 in stretches, 20,000 tokens 1,481
+// and 1,272.  Two groups, 64 to 90 x 8 to 32 x 2 sums: in stretches 0.5-1% slower
+// (the workgroups then read all over the launch's part of the arena).
+constexpr uint64_t kDirectStretchTags = 8192;
 
 struct VerifyParams {
   const TagPair* partials;
@@ -376,7 +387,7 @@ hipError_t launch_scatter(const ScatterParams& p, hipStream_t s);
 
 hipError_t launch_install(const InstallParams& p, uint32_t n_workgroups, hipStream_t s,
                           hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-hipError_t launch_install_direct(const DirectParams& p, hipStream_t s, hipEvent_t start = nullptr,
+hipError_t launch_install_direct(DirectParams p, hipStream_t s, hipEvent_t start = nullptr,
                                  hipEvent_t stop = nullptr);
 hipError_t launch_verify(const VerifyParams& p, hipStream_t s);
 hipError_t launch_stage(const StageRun* runs, uint32_t n_runs, hipStream_t s, hipEvent_t start = nullptr,

@@ -386,19 +386,13 @@ __device__ __forceinline__ uint32_t add_if_ge(uint32_t acc, uint32_t a, uint32_t
   return acc;
 }
 
-// One work item.  bid: its index in dispatch order.  kDirect: the chunk is
-// read from chunk_src[c] (the device's view of pinned memory) instead of its
-// ring slot, and the words' sum and XOR go to acc[c][group], in LDS, instead
-// of a tag partial.
-template <bool kDirect>
-__device__ __forceinline__ void install_piece(const InstallHead& H, const BSR_KERNARG InstallGroup* groups,
-                                              const uint8_t* const BSR_KERNARG* chunk_src, TagPair* acc, uint32_t bid,
+// One work item.  bid: its index in dispatch order.
+__device__ __forceinline__ void install_piece(const InstallHead& H, const BSR_KERNARG InstallGroup* groups, uint32_t bid,
                                               uint8_t* lds, uint32_t tid) {
   const uint32_t lane = tid & 63;
-  // words in flight per thread of an unaligned piece: over the link a whole
-  // contiguous piece, out of HBM enough to leave the registers of the main
-  // path alone
-  constexpr uint32_t kWords = kDirect ? kMaxPieceBytes / (4 * kInstallThreads) : 4;
+  // words in flight per thread of an unaligned piece: enough to leave the
+  // registers of the main path alone
+  constexpr uint32_t kWords = 4;
   // Every wave runs this decode before its first data load, and that delay
   // costs bandwidth, so it is kept short: about 120 scalar instructions
   // (256 extra ones per wave cost a plain copy of this shape about 3 points
@@ -421,14 +415,9 @@ __device__ __forceinline__ void install_piece(const InstallHead& H, const BSR_KE
   const uint32_t j = r1 - t * G.segs_per_chunk;
 
   const uint32_t chunk = H.first_chunk + c;
-  const uint8_t* base;
-  if constexpr (kDirect) {
-    base = chunk_src[c];
-  } else {
-    const uint32_t slot0 = H.first_slot + c;  // c < n_chunks <= W
-    const uint32_t slot = slot0 >= H.window ? slot0 - H.window : slot0;
-    base = H.ring + static_cast<uint64_t>(slot) * H.slot_bytes;
-  }
+  const uint32_t slot0 = H.first_slot + c;  // c < n_chunks <= W
+  const uint32_t slot = slot0 >= H.window ? slot0 - H.window : slot0;
+  const uint8_t* base = H.ring + static_cast<uint64_t>(slot) * H.slot_bytes;
   // Token positions in 32 bits: the bound prefix plus two blocks stays
   // below 2^32 tokens (checked when the request is bound).
   const uint32_t C = H.chunk_tokens, B = G.block_tokens;
@@ -516,7 +505,6 @@ __device__ __forceinline__ void install_piece(const InstallHead& H, const BSR_KE
         uint8_t* blk = md.tensor_base + static_cast<uint64_t>(md.block) * G.block_bytes;
         uint8_t* dst1 = blk + (o0 + u0) * sp;
         uint8_t* dst2 = blk + (B * sp + (o0 + u0) * (r - sp));
-        if constexpr (kDirect) __syncthreads();  // the workgroup's previous piece has left the LDS
         if (src_ok && ((reinterpret_cast<uintptr_t>(dst1) & 15u) | (reinterpret_cast<uintptr_t>(dst2) & 3u)) == 0)
           planar_from_regs(v, nvec, dst1, dst2, mu, r, sp, G.div_p1, G.div_p2, lds, tid, s, x);
         else
@@ -527,19 +515,11 @@ __device__ __forceinline__ void install_piece(const InstallHead& H, const BSR_KE
 
   s = wave_sum(s);
   x = wave_xor(x);
-  if constexpr (kDirect) {
-    if (lane == 0) {
-      TagPair* a = acc + c * BSR_MAX_GROUPS + G.group;
-      atomicAdd(&a->sum, s);
-      atomicXor(&a->x, x);
-    }
-  } else {
-    // one tag partial per wave: TagPair {sum, xor} as one little-endian 8-byte word
-    static_assert(sizeof(TagPair) == 8 && offsetof(TagPair, x) == 4, "sum in the low word");
-    if (lane == 0)
-      *global_ptr(reinterpret_cast<uint64_t*>(H.partials) + wg * kInstallWaves + (tid >> 6)) =
-          static_cast<uint64_t>(s) | (static_cast<uint64_t>(x) << 32);
-  }
+  // one tag partial per wave: TagPair {sum, xor} as one little-endian 8-byte word
+  static_assert(sizeof(TagPair) == 8 && offsetof(TagPair, x) == 4, "sum in the low word");
+  if (lane == 0)
+    *global_ptr(reinterpret_cast<uint64_t*>(H.partials) + wg * kInstallWaves + (tid >> 6)) =
+        static_cast<uint64_t>(s) | (static_cast<uint64_t>(x) << 32);
 }
 
 __global__ __launch_bounds__(kInstallThreads) void k_install(const InstallParams p) {
@@ -548,22 +528,218 @@ __global__ __launch_bounds__(kInstallThreads) void k_install(const InstallParams
   const InstallHead H = load_args(&q->h);
   // work index -> dispatch position (the group), then (chunk, piece within
   // the chunk's group range)
-  install_piece<false>(H, q->g, nullptr, nullptr, xcd_work_index(blockIdx.x, H.xcd_full, H.xcd_log2), lds, threadIdx.x);
+  install_piece(H, q->g, xcd_work_index(blockIdx.x, H.xcd_full, H.xcd_log2), lds, threadIdx.x);
 }
 
 // The same work with no ring in between: chunks go from pinned memory over
-// the host link straight into their blocks.  For requests on one stream, where
-// staging copy, install and verify run one after the other: three launches,
-// about 10 us apart, become one, and the install's own time goes.  Bound by
-// the link, so a small grid takes the pieces in turn, one piece of loads in
-// flight per workgroup.  Measured in turn with the three launches: 1K tokens
-// in 147 KB chunks at W = 2 (2.4 MB) 176 -> 96 us per request, 1,287 tokens of
-// eight ragged groups (3.5 MB) 249 -> 133 us, 63 MB of 64-token chunks 1,268
-// -> 1,180 us.  The launch verifies itself: a workgroup sums the tags of
-// its pieces per (chunk, group) in LDS and adds them to the shared words when
-// it is done; the first workgroup also takes the stored tags off, so a
-// matching entry ends at zero, and the last one to finish applies the first
-// mismatching chunk as k_verify does.
+// the host link straight into their blocks, and the launch checks its tags.
+//
+// A piece as the direct install sees it: the whole 16-byte vectors that cover
+// it, read from pinned memory, and where its bytes go.  (A chunk's source is
+// 16-byte aligned and its groups' entries are padded to 256 bytes, so the
+// covering vectors never leave it.)
+struct DirectPiece {
+  const uint8_t* src;  // of the piece's first byte
+  uint32_t bytes;      // 0: nothing to install
+  uint32_t nvec;       // covering vectors held in registers; 0: the piece is too large for them
+  uint32_t lead;       // bytes of the first vector before the piece
+  uint32_t entry;      // chunk of the launch * BSR_MAX_GROUPS + group
+  uint32_t kind, record, split;
+  uint32_t tokens;     // PLANAR: records in the piece
+  uint32_t block_bytes, pool_blocks;
+  uint32_t off1, off2; // in the block: of the piece (CONTIG), of its part of each plane (PLANAR)
+  PackedDiv d1, d2;
+  const int32_t* block;        // its block table entry
+  uint8_t* const* tensor_base;
+};
+
+constexpr uint32_t kDirectVecs = kPlanarVecs;  // vectors per thread
+
+__device__ __forceinline__ DirectPiece direct_piece(const BSR_KERNARG DirectParams* q, uint32_t bid) {
+  const InstallHead H = load_args(&q->ip.h);
+  uint32_t oi = 0;
+#pragma unroll
+  for (uint32_t o = 1; o < BSR_MAX_GROUPS; ++o) oi = add_if_ge(oi, bid, H.start[o]);
+  const InstallGroup G = load_args(&q->ip.g[oi]);
+  uint32_t rem = bid - H.n_chunks * G.prefix;
+  const uint32_t c = packed_div(G.div_per_chunk.m, G.div_per_chunk.s, rem);
+  rem -= c * G.per_chunk;
+  const uint32_t r1 = packed_div(G.div_pieces.m, G.div_pieces.s, rem);
+  const uint32_t piece = rem - r1 * G.pieces_per_seg;
+  const uint32_t t = packed_div(G.div_segs.m, G.div_segs.s, r1);
+  const uint32_t j = r1 - t * G.segs_per_chunk;
+  const uint32_t C = H.chunk_tokens, B = G.block_tokens, r = G.record_bytes;
+  const uint32_t tok0 = (H.first_chunk + c) * C;
+  const uint32_t k = packed_div(G.div_block.m, G.div_block.s, tok0) + j;  // request block index
+  const uint32_t blo = k * B;
+  const uint32_t lo = tok0 > blo ? tok0 : blo;
+  const uint32_t hi = (tok0 + C) < (blo + B) ? (tok0 + C) : (blo + B);
+  const bool some = lo < hi && k < G.n_blocks;
+  const uint32_t m = some ? hi - lo : 0, o0 = lo - blo;
+
+  DirectPiece P;
+  P.kind = G.kind;
+  P.record = r;
+  P.split = G.split_bytes;
+  P.entry = c * BSR_MAX_GROUPS + G.group;
+  P.block_bytes = G.block_bytes;
+  P.pool_blocks = G.pool_blocks;
+  P.d1 = G.div_p1;
+  P.d2 = G.div_p2;
+  P.block = G.block_table + (some ? k : 0);
+  P.tensor_base = G.tensor_bases + t;
+  uint32_t off = piece * G.piece;  // CONTIG: bytes
+  if (G.kind == BSR_KIND_CONTIG) {
+    const uint32_t seg = m * r;
+    P.bytes = off < seg ? ((seg - off) < G.piece ? (seg - off) : G.piece) : 0;
+    P.tokens = 0;
+    P.off1 = o0 * r + off;
+    P.off2 = 0;
+  } else {
+    const uint32_t u0 = off;
+    P.tokens = u0 < m ? ((m - u0) < G.piece ? (m - u0) : G.piece) : 0;
+    P.bytes = P.tokens * r;
+    P.off1 = (o0 + u0) * G.split_bytes;
+    P.off2 = B * G.split_bytes + (o0 + u0) * (r - G.split_bytes);
+    off = u0 * r;
+  }
+  P.src = q->src[c] + (G.staged_off + (t * C + (lo - tok0)) * r + off);
+  P.lead = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(P.src)) & 15u;
+  P.nvec = P.bytes ? (P.lead + P.bytes + 15u) >> 4 : 0;
+  if (P.nvec > kDirectVecs * kInstallThreads || P.nvec * 16u > (H.lds_bytes >> 1)) P.nvec = 0;
+  return P;
+}
+
+// A piece's loads: its vectors (those past its end return zero and read
+// nothing), then one word per lane of where it goes: lane 0 the block id,
+// lanes 1 and 2 the halves of the tensor base.
+struct DirectLoads {
+  i32x4 v[kDirectVecs];
+  uint32_t meta;
+};
+
+__device__ __forceinline__ DirectLoads direct_load(const DirectPiece& P, uint32_t tid) {
+  DirectLoads L;
+  const __amdgpu_buffer_rsrc_t r = piece_rsrc(const_cast<uint8_t*>(P.src - P.lead), P.nvec * 16u);
+#pragma unroll
+  for (uint32_t u = 0; u < kDirectVecs; ++u)
+    L.v[u] = __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>((u * kInstallThreads + tid) * 16u), 0, 0);
+  const uint32_t lane = tid & 63;
+  const uint32_t* a = reinterpret_cast<const uint32_t*>(P.block);
+  if (lane == 1 || lane == 2) a = reinterpret_cast<const uint32_t*>(P.tensor_base) + (lane - 1);
+  L.meta = *global_ptr(a);
+  return L;
+}
+
+// LDS traffic only: the loads of the next piece stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Store a piece that has arrived.  Contiguous pieces of whole aligned vectors
+// go straight from the registers; all others through the LDS, in one half of
+// it and the next one in the other (`half`), so that one barrier a piece is
+// enough.
+__device__ __forceinline__ void direct_store(const DirectPiece& P, const DirectLoads& L, TagPair* acc, uint8_t* lds,
+                                             uint32_t lds_half, uint32_t& half, uint32_t tid) {
+  const uint32_t lane = tid & 63;
+  const int32_t b = static_cast<int32_t>(row_lane(L.meta, 0));
+  const uint64_t lo = row_lane(L.meta, 1), hi = row_lane(L.meta, 2);
+  if (P.bytes == 0 || b < 0 || static_cast<uint32_t>(b) >= P.pool_blocks) return;
+  uint8_t* blk = reinterpret_cast<uint8_t*>(lo | (hi << 32)) + static_cast<uint64_t>(b) * P.block_bytes;
+  uint8_t* dst1 = blk + P.off1;
+  uint8_t* dst2 = blk + P.off2;
+  const bool whole = ((P.lead | P.bytes) & 15u) == 0;
+  const uint32_t rw = P.record >> 2, sw = P.split >> 2, nw = P.bytes >> 2;
+  uint32_t s = 0, x = 0;
+  if (P.nvec == 0) {  // larger than the registers
+    constexpr uint32_t kWords = 16;
+    if (P.kind == BSR_KIND_CONTIG)
+      copy_words<kWords>(P.src, dst1, P.bytes, tid, s, x);
+    else
+      planar_words<kWords>(P.src, dst1, dst2, P.tokens, P.record, P.split, tid, s, x);
+  } else if (P.kind == BSR_KIND_CONTIG && whole && (reinterpret_cast<uintptr_t>(dst1) & 15u) == 0) {
+    const __amdgpu_buffer_rsrc_t rs = piece_rsrc(dst1, P.bytes);
+    static_assert(kMaxPieceBytes <= BSR_UNROLL * kPieceAlign, "a contiguous piece is BSR_UNROLL vectors per thread");
+#pragma unroll
+    for (uint32_t u = 0; u < BSR_UNROLL; ++u) {
+      const u32x4 v = __builtin_bit_cast(u32x4, L.v[u]);
+      fold(v, s, x);  // zeros past the end
+      st_piece16(v, rs, (u * kInstallThreads + tid) * 16u);
+    }
+  } else {
+    uint8_t* at = lds + half * lds_half;
+    half ^= 1u;
+    u32x4* l4 = reinterpret_cast<u32x4*>(at);
+#pragma unroll
+    for (uint32_t u = 0; u < kDirectVecs; ++u) {
+      const uint32_t i = u * kInstallThreads + tid;
+      const u32x4 v = __builtin_bit_cast(u32x4, L.v[u]);
+      if (whole) fold(v, s, x);
+      if (i < P.nvec) l4[i] = v;
+    }
+    lds_barrier();
+    const uint32_t* l1 = reinterpret_cast<const uint32_t*>(at + P.lead);  // the piece's words
+    if (!whole)
+      for (uint32_t i = tid; i < nw; i += kInstallThreads) {
+        const uint32_t w = l1[i];
+        s += w;
+        x ^= w;
+      }
+    if (P.kind == BSR_KIND_CONTIG) {
+      const __amdgpu_buffer_rsrc_t rs = piece_rsrc(dst1, P.bytes);
+      for (uint32_t i = tid; i < nw; i += kInstallThreads) st_piece4(l1[i], rs, i * 4u);
+    } else {
+      const __amdgpu_buffer_rsrc_t rs1 = piece_rsrc(dst1, P.tokens * P.split);
+      const __amdgpu_buffer_rsrc_t rs2 = piece_rsrc(dst2, P.tokens * (P.record - P.split));
+      if (((P.split | static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst1))) & 15u) == 0) {
+        const uint32_t vpt = P.split >> 4, n1 = P.tokens * vpt;
+        for (uint32_t i = tid; i < n1; i += kInstallThreads) {  // vector i covers token i / vpt, part i % vpt
+          const uint32_t tk = packed_div(P.d1.m, P.d1.s, i);
+          const uint32_t w0 = tk * rw + (i - tk * vpt) * 4;
+          const u32x4 v{l1[w0], l1[w0 + 1], l1[w0 + 2], l1[w0 + 3]};
+          st_piece16(v, rs1, i * 16u);
+        }
+      } else {
+        const uint32_t n1 = P.tokens * sw;
+        for (uint32_t i = tid; i < n1; i += kInstallThreads) {
+          const uint32_t tk = i / sw;
+          st_piece4(l1[tk * rw + (i - tk * sw)], rs1, i * 4u);
+        }
+      }
+      const uint32_t w2 = rw - sw, n2 = P.tokens * w2;
+      for (uint32_t i = tid; i < n2; i += kInstallThreads) {
+        const uint32_t tk = packed_div(P.d2.m, P.d2.s, i);
+        st_piece4(l1[tk * rw + sw + (i - tk * w2)], rs2, i * 4u);
+      }
+    }
+  }
+  s = wave_sum(s);
+  x = wave_xor(x);
+  if (lane == 0) {
+    atomicAdd(&acc[P.entry].sum, s);
+    atomicXor(&acc[P.entry].x, x);
+  }
+}
+
+// For requests whose staging copy, install and verify would run one after the
+// other, or would share the link with another request's: three launches,
+// about 10 us apart, become one, and the install's own time goes.  Bound by the
+// link, so a small grid takes the pieces in turn; each workgroup issues a
+// piece's loads before it stores the piece before (two in flight), so that
+// half the workgroups keep the link as busy as with one piece each (kDirectInflight).
+// Measured in turn, one and two pieces in flight per workgroup: 75 MB of two
+// groups 1,387 and 1,378 us per request (57.5 GB/s of link take 1,308), 621 MB
+// 11,061 and 10,990 (10,805), 46 MB of one group 1,035 and 1,017 (800), 55 MB of
+// eight ragged groups, whose unaligned pieces were read as words, 1,534 and
+// 1,481 (960), and 1,272 in stretches (kDirectStretchTags).
+// The launch verifies itself: a workgroup sums the tags of its pieces per
+// (chunk, group) in LDS and adds them to the shared words when it is done; the
+// first workgroup also takes the stored tags off, so a matching entry ends at
+// zero, and the last one to finish applies the first mismatching chunk as
+// k_verify does.
 __global__ __launch_bounds__(kInstallThreads) void k_install_direct(const DirectParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   __shared__ TagPair acc[BSR_MAX_INSTALL_BATCH * BSR_MAX_GROUPS];
@@ -579,15 +755,51 @@ __global__ __launch_bounds__(kInstallThreads) void k_install_direct(const Direct
     acc[i] = t;
   }
   if (tid < BSR_MAX_INSTALL_BATCH) bad[tid] = 0;
+  // Prefix check, once: a failure recorded by an earlier chunk, or an invalid
+  // group, puts the launch past the valid prefix.  Nothing writes the status
+  // words while installs run but the last workgroup, when all are done.
+  bool live = p.status->fail == 0;
+  for (uint32_t g = 0; g < p.ip.h.n_groups; ++g) live = live && p.status->q[g] != 0;
   __syncthreads();
-  const uint32_t total = n_chunks * p.ip.h.wg_per_chunk, grid = gridDim.x;
-  for (uint32_t b = blockIdx.x; b < total; b += grid) {
-    // The arguments are read again for every piece: kept across the loop, they
-    // take more scalar registers than there are.
-    const auto* q = (const BSR_KERNARG DirectParams*)(__builtin_amdgcn_kernarg_segment_ptr());
+  const uint32_t total = live ? n_chunks * p.ip.h.wg_per_chunk : 0, grid = gridDim.x;
+  const uint32_t lds_half = (p.ip.h.lds_bytes >> 1) & ~15u;
+  // Pieces in turn, so that the workgroups read adjacent ones at a time; or one
+  // stretch of them each, so that a workgroup adds to the tags of few chunks.
+  uint32_t next = blockIdx.x, step = grid, end = total, half = 0;
+  if (p.stretches) {
+    const uint32_t each = total / grid, more = total - each * grid;  // the first `more` take one piece more
+    next = blockIdx.x * each + (blockIdx.x < more ? blockIdx.x : more);
+    end = next + each + (blockIdx.x < more ? 1u : 0u);
+    step = 1;
+  }
+  // The arguments are read again for every piece: kept across the loop, they
+  // take more scalar registers than there are.
+  const auto* q = (const BSR_KERNARG DirectParams*)(__builtin_amdgcn_kernarg_segment_ptr());
+  auto decode = [&](uint32_t b) {
     asm volatile("" : "+s"(q));
-    const InstallHead H = load_args(&q->ip.h);
-    install_piece<true>(H, q->ip.g, q->src, acc, b, lds, tid);
+    return direct_piece(q, b);
+  };
+  if (next < end) {
+    DirectPiece pa = decode(next);
+    DirectLoads la = direct_load(pa, tid);
+    for (;;) {
+      next += step;
+      if (next >= end) {
+        direct_store(pa, la, acc, lds, lds_half, half, tid);
+        break;
+      }
+      const DirectPiece pb = decode(next);
+      const DirectLoads lb = direct_load(pb, tid);
+      direct_store(pa, la, acc, lds, lds_half, half, tid);
+      next += step;
+      if (next >= end) {
+        direct_store(pb, lb, acc, lds, lds_half, half, tid);
+        break;
+      }
+      pa = decode(next);
+      la = direct_load(pa, tid);
+      direct_store(pb, lb, acc, lds, lds_half, half, tid);
+    }
   }
   __syncthreads();
   VerifyAux* aux = p.aux;
@@ -615,8 +827,6 @@ __global__ __launch_bounds__(kInstallThreads) void k_install_direct(const Direct
     // writes the status words, and only here
     bsr_dev_status* st = p.status;
     const uint32_t n_groups = p.ip.h.n_groups;
-    bool live = st->fail == 0;
-    for (uint32_t g = 0; g < n_groups; ++g) live = live && st->q[g] != 0;
     const uint32_t m = tid < n_chunks ? bad[tid] : 0u;
     const uint64_t any = __ballot(m != 0u);
     if (live && any != 0ull && tid == static_cast<uint32_t>(__builtin_ctzll(any))) {
@@ -982,14 +1192,15 @@ hipError_t launch_install(const InstallParams& p, uint32_t n_workgroups, hipStre
   return hipGetLastError();
 }
 
-hipError_t launch_install_direct(const DirectParams& p, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+hipError_t launch_install_direct(DirectParams p, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const uint64_t total = static_cast<uint64_t>(p.ip.h.n_chunks) * p.ip.h.wg_per_chunk;
   if (p.ip.h.n_chunks == 0 || p.ip.h.n_chunks > BSR_MAX_INSTALL_BATCH || total >= (1ull << 31)) return hipErrorInvalidValue;
   for (uint32_t i = 0; i < p.ip.h.n_chunks; ++i)
     if (!p.src[i] || (reinterpret_cast<uintptr_t>(p.src[i]) & 15u)) return hipErrorInvalidValue;
   const uint64_t bytes = p.ip.h.n_chunks * p.ip.h.slot_bytes;
-  const uint64_t want = std::min({kDirectMaxGrid, kDirectInflight * total / bytes + 1, total / 2});
+  const uint64_t want = std::min({kDirectMaxGrid, kDirectInflight * total / (2 * bytes) + 1, total / kDirectMinPieces});
   const uint32_t grid = static_cast<uint32_t>(std::min(std::max(kDirectMinGrid, want), total));
+  p.stretches = static_cast<uint64_t>(grid) * p.ip.h.n_chunks * p.ip.h.n_groups >= kDirectStretchTags ? 1u : 0u;
   if (start && stop)
     hipExtLaunchKernelGGL(k_install_direct, dim3(grid), dim3(kInstallThreads), p.ip.h.lds_bytes, s, start, stop, 0, p);
   else

@@ -252,6 +252,22 @@ def test_install_straight_from_pinned_memory(groups, C, n_chunks, W, bad):
         gc.close()
 
 
+# records larger than the registers hold, beside unaligned ones; a planar piece
+# that fits them only when it starts on a vector (tensor 0 does, 1 does not);
+# planes whose values are no whole vectors; eight groups in enough pieces for
+# workgroups to take stretches of them, in launches of 32 and of 13 chunks
+DIRECT_PIECES = [([(4, 1, 24_000, 128), (3, 2, 20, 0)], 4, 9, 4), ([(2048, 2, 20, 16)], 1027, 3, 2),
+                 ([(16, 2, 28, 12), (48, 1, 2048, 0)], 24, 7, 3),
+                 ([(8, 2, 64, 0), (16, 1, 36, 32), (64, 3, 20, 0), (24, 2, 132, 128), (32, 1, 1152, 0), (5, 2, 12, 0),
+                   (48, 1, 24, 8), (128, 2, 512, 0)], 32, 45, 32)]
+
+
+@pytest.mark.parametrize("groups,C,n_chunks,W", DIRECT_PIECES)
+@pytest.mark.parametrize("bad", [None, "last"])
+def test_direct_pieces_at_the_limits_of_the_registers(groups, C, n_chunks, W, bad):
+    test_install_straight_from_pinned_memory(groups, C, n_chunks, W, bad)
+
+
 def test_direct_and_staged_chunks_in_one_request(tmp_path):
     """Runs of chunks from the pinned store and from files alternate: the
     former are installed straight from there, the latter through the ring."""
