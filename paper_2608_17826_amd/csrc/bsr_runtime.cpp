@@ -133,25 +133,76 @@ bool host_is_little_endian() {
   return b == 1;
 }
 
-// d_i for every full chunk, data-parallel over chunks for long inputs.
+// d_i for every full chunk.  One digest is a serial chain, an XOR and a 64-bit
+// multiply per byte (4-5 cycles), so several chunks are hashed side by side:
+// four in scalar registers, or 32 in four vectors where the CPU multiplies
+// 64-bit lanes.  512 chunks of 256 tokens on the EPYC host of an MI355X: one by
+// one 405 us (1.3 GB/s), four 105, 32 37 us (14 GB/s); on a 2.7 GHz Xeon 795, 223
+// and 155, with 256-bit vectors 280.
+using DigestRange = void (*)(const int32_t*, uint64_t, uint64_t, uint32_t, uint64_t*);
+
+void digest_range(const int32_t* tokens, uint64_t lo, uint64_t hi, uint32_t C, uint64_t* d) {
+  constexpr uint64_t kLanes = 4;
+  uint64_t i = lo;
+  for (; i + kLanes <= hi; i += kLanes) {
+    uint64_t h[kLanes];
+    for (uint64_t& x : h) x = kFnvBasis;
+    for (uint64_t b = 0; b < static_cast<uint64_t>(C) * 4; ++b)
+      for (uint64_t l = 0; l < kLanes; ++l)
+        h[l] = (h[l] ^ reinterpret_cast<const uint8_t*>(tokens + (i + l) * C)[b]) * kFnvPrime;
+    for (uint64_t l = 0; l < kLanes; ++l) d[i + l] = h[l];
+  }
+  for (; i < hi; ++i) d[i] = fnv1a64(reinterpret_cast<const uint8_t*>(tokens + i * C), static_cast<uint64_t>(C) * 4);
+}
+
+#if defined(__x86_64__)
+__attribute__((target("avx512f,avx512dq"))) void digest_range_avx512(const int32_t* tokens, uint64_t lo, uint64_t hi,
+                                                                     uint32_t C, uint64_t* d) {
+  typedef uint64_t u64x8 __attribute__((vector_size(64)));
+  constexpr uint32_t kVecs = 4, kLanes = 8 * kVecs;
+  // the last few chunks are no slower in scalar registers than in vectors that
+  // are mostly idle (Xeon, 64-token chunks: 16 take 2.0 and 2.5 us, 31 4.7 and 3.2)
+  constexpr uint64_t kLeast = 20;
+  uint64_t i = lo;
+  for (; i + kLeast <= hi; i += std::min<uint64_t>(kLanes, hi - i)) {
+    const uint64_t n = std::min<uint64_t>(kLanes, hi - i);
+    const int32_t* at[kLanes];  // lanes past the last chunk hash it again
+    for (uint64_t l = 0; l < kLanes; ++l) at[l] = tokens + (i + (l < n ? l : n - 1)) * C;
+    u64x8 h[kVecs];
+    for (u64x8& v : h) v = u64x8{} + kFnvBasis;
+    for (uint32_t t = 0; t < C; ++t) {
+      u64x8 w[kVecs];
+      for (uint32_t v = 0; v < kVecs; ++v)
+        for (uint32_t l = 0; l < 8; ++l) w[v][l] = static_cast<uint32_t>(at[8 * v + l][t]);
+      for (int byte = 0; byte < 4; ++byte)  // little-endian host (checked at entry)
+        for (uint32_t v = 0; v < kVecs; ++v) {
+          h[v] = (h[v] ^ (w[v] & 0xff)) * kFnvPrime;
+          w[v] >>= 8;
+        }
+    }
+    for (uint64_t l = 0; l < n; ++l) d[i + l] = h[l / 8][l % 8];
+  }
+  digest_range(tokens, i, hi, C, d);
+}
+#endif
+
+// Data-parallel over chunks for long inputs.
 void chunk_digests(const int32_t* tokens, uint64_t n_chunks, uint32_t C, uint64_t* d) {
-  const uint64_t bytes = static_cast<uint64_t>(C) * 4;
-  auto work = [&](uint64_t lo, uint64_t hi) {
-    for (uint64_t i = lo; i < hi; ++i)
-      d[i] = fnv1a64(reinterpret_cast<const uint8_t*>(tokens + i * C), bytes);
-  };
-  const uint64_t total = n_chunks * bytes;
-  unsigned nt = std::thread::hardware_concurrency();
-  if (nt > 8) nt = 8;
-  if (total < (1u << 20) || nt <= 1 || n_chunks < 2 * nt) {
-    work(0, n_chunks);
+  DigestRange range = digest_range;
+#if defined(__x86_64__)
+  if (__builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512dq")) range = digest_range_avx512;
+#endif
+  unsigned nt = 1;  // asking for the CPUs is a system call of 4 us: long inputs only
+  if (n_chunks * C * 4 >= (1u << 20)) nt = std::min(8u, std::thread::hardware_concurrency());
+  if (nt <= 1 || n_chunks < 2 * nt) {
+    range(tokens, 0, n_chunks, C, d);
     return;
   }
   std::vector<std::thread> th;
   const uint64_t per = (n_chunks + nt - 1) / nt;
   for (unsigned t = 0; t < nt; ++t) {
     const uint64_t lo = t * per, hi = std::min(n_chunks, lo + per);
-    if (lo < hi) th.emplace_back(work, lo, hi);
+    if (lo < hi) th.emplace_back(range, tokens, lo, hi, C, d);
   }
   for (auto& x : th) x.join();
 }

@@ -70,6 +70,25 @@ def test_chunk_keys_bit_exact(C, n, salt):
     assert [int(x) for x in bsr.bsr_chunk_keys(salt, toks, C)] == oracle.chain_keys(toks, C, salt)
 
 
+@pytest.mark.parametrize("C,n_chunks", [(1, 1), (5, 3), (3, 4), (16, 19), (7, 20), (64, 31), (64, 33), (9, 51), (2, 52),
+                                        (33, 83), (256, 1023), (256, 1024), (4096, 70)])
+def test_chunk_keys_side_by_side(C, n_chunks):
+    """Chunk counts around the numbers that are hashed together (4, 20, 32),
+    and inputs just below and from 1 MiB on, which threads share."""
+    toks = np.random.default_rng(C * n_chunks).integers(-2**31, 2**31, n_chunks * C + C // 2, dtype=np.int64).astype(np.int32)
+    h, want = 11, []
+    with np.errstate(over="ignore"):
+        d = np.full(n_chunks, 0xcbf29ce484222325, dtype=np.uint64)
+        for column in toks[:n_chunks * C].reshape(n_chunks, C).view(np.uint8).T:
+            d = (d ^ column) * np.uint64(0x100000001b3)
+    for i in range(n_chunks):
+        h = oracle.fnv1a64(h.to_bytes(8, "little") + int(d[i]).to_bytes(8, "little"))
+        want.append(h)
+    assert [int(x) for x in bsr.bsr_chunk_keys(11, toks, C)] == want
+    if n_chunks < 100:
+        assert want == oracle.chain_keys(toks, C, 11)
+
+
 def _host_ctx(w, W=2):
     ctx = bsr.bsr_ctx_create(_layout(w), W, hip_device=-1)
     slot = bsr.bsr_slot_bytes(ctx.layout)
