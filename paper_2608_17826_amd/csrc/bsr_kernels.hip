@@ -19,9 +19,10 @@
 //           a values plane and a scales plane inside a block) stage the
 //           piece in LDS and write both planes with coalesced stores.  Every
 //           wave folds the words it read into a (sum, xor) tag partial.
-// direct  : the install of a small request, reading pinned memory over the
-//           host link itself (no staging copy, no ring), and checking its
-//           tags in the same launch.
+// direct  : the install of requests whose staging could not run beside their
+//           own installs or would share the link: it reads pinned memory over
+//           the host link itself (no staging copy, no ring) and checks its tags
+//           in the same launch.
 // verify  : reduce the partials of each (chunk, group) and compare with the
 //           tag recorded at store time; the first mismatching chunk, in
 //           chunk order, fails the request (q_g = 0 for its mismatching
