@@ -775,8 +775,8 @@ __global__ __launch_bounds__(kInstallThreads) void k_install_direct(const Direct
   }
   // The arguments are read again for every piece: kept across the loop, they
   // take more scalar registers than there are.
-  const auto* q = (const BSR_KERNARG DirectParams*)(__builtin_amdgcn_kernarg_segment_ptr());
-  auto decode = [&](uint32_t b) {
+  auto decode = [](uint32_t b) {
+    const auto* q = (const BSR_KERNARG DirectParams*)(__builtin_amdgcn_kernarg_segment_ptr());
     asm volatile("" : "+s"(q));
     return direct_piece(q, b);
   };
