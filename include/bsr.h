@@ -441,7 +441,8 @@ int bsr_probe(bsr_ctx* ctx, uint64_t request_id, uint64_t salt, const int32_t* t
  * own staging rings and status blocks (overlap -> BSR_E_ARG) and must not
  * share destination blocks; they may share streams.  n_hit_chunks <= the
  * probed n, and n_hit_chunks * chunk_tokens plus twice the largest
- * block_tokens must stay below 2^32 (else BSR_E_ARG).
+ * block_tokens must stay below 2^32, and the blocks that the prefix needs,
+ * all groups together, must not exceed 2^32 - 2^18 (else BSR_E_ARG).
  * dst: n_groups destinations (block tables are copied to the host once and
  * checked: every id < pool_blocks, no id repeated -> else BSR_E_ARG; with
  * BSR_FLAG_TRUSTED_TABLES they are checked on the device instead, see the

@@ -291,6 +291,20 @@ enum FinishMode : uint32_t {
   kFinishCheckTables = 4, // fail the request if an advertised block id is outside its pool
 };
 
+constexpr uint32_t kFinishThreads = 256;
+constexpr uint32_t kFinishMaxGrid = 1024;  // workgroups; each thread takes every (grid x threads)-th block
+// Block table entries of one request, all groups together: the finishing
+// kernel's index, plus one stride, stays below 2^32.
+constexpr uint64_t kMaxRequestBlocks = (1ull << 32) - kFinishMaxGrid * kFinishThreads;
+
+// Blocks that `tokens` tokens advertise in one group, and in all groups.
+inline uint64_t group_blocks(uint64_t tokens, uint32_t block_tokens) { return (tokens + block_tokens - 1) / block_tokens; }
+inline uint64_t request_blocks(uint64_t tokens, const uint32_t* block_tokens, uint32_t n_groups) {
+  uint64_t n = 0;
+  for (uint32_t g = 0; g < n_groups; ++g) n += group_blocks(tokens, block_tokens[g]);
+  return n;
+}
+
 struct FinishParams {
   bsr_dev_status* status;
   VerifyAux* verify_aux;    // begin: zeroed
@@ -299,7 +313,7 @@ struct FinishParams {
   uint32_t reason;          // invalidate: BSR_FAIL_*
   uint32_t chunk;           // invalidate: failing chunk or BSR_NO_CHUNK
   uint32_t group_mask;      // invalidate: groups whose q_g becomes 0; mark: the group
-  uint32_t total_blocks;    // sum of n_req_blocks
+  uint32_t total_blocks;    // sum of n_req_blocks (<= kMaxRequestBlocks)
   uint32_t chunk_tokens;
   uint64_t exposed_if_valid;
   bsr_dev_status* mirror;   // commit: the status block is also written here (pinned host memory); may be null

@@ -923,7 +923,7 @@ __global__ __launch_bounds__(kVerifyThreads) void k_verify(const VerifyParams p)
   }
 }
 
-__global__ __launch_bounds__(256) void k_finish(const FinishParams p) {
+__global__ __launch_bounds__(kFinishThreads) void k_finish(const FinishParams p) {
   const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
   bsr_dev_status* st = p.status;
   uint8_t value = 0;
@@ -1246,10 +1246,11 @@ hipError_t launch_verify(const VerifyParams& p, hipStream_t s) {
 }
 
 hipError_t launch_finish(const FinishParams& p, hipStream_t s) {
-  uint32_t grid = (p.total_blocks + 255) / 256;
+  if (p.total_blocks > kMaxRequestBlocks) return hipErrorInvalidValue;
+  uint32_t grid = (p.total_blocks + kFinishThreads - 1) / kFinishThreads;
   if (grid == 0) grid = 1;
-  if (grid > 1024) grid = 1024;
-  hipLaunchKernelGGL(k_finish, dim3(grid), dim3(256), 0, s, p);
+  if (grid > kFinishMaxGrid) grid = kFinishMaxGrid;
+  hipLaunchKernelGGL(k_finish, dim3(grid), dim3(kFinishThreads), 0, s, p);
   return hipGetLastError();
 }
 

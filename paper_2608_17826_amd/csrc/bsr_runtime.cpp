@@ -1460,11 +1460,16 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
   ip.h.lds_bytes = c->geo.lds_bytes;
   ip.h.xcd_log2 = c->xcd_log2;
   ip.h.status = status;
-  uint32_t total = 0;
+  uint32_t block_tokens[BSR_MAX_GROUPS];
+  for (uint32_t g = 0; g < G; ++g) block_tokens[g] = c->geo.L.groups[g].block_tokens;
+  const uint64_t total = bsr::request_blocks(static_cast<uint64_t>(n_hit) * C, block_tokens, G);
+  if (total > bsr::kMaxRequestBlocks)
+    return fail_with(BSR_E_ARG, "the prefix needs %llu block table entries over all groups, at most %llu",
+                     (unsigned long long)total, (unsigned long long)bsr::kMaxRequestBlocks);
   for (uint32_t g = 0; g < G; ++g) {
     const bsr_group_dst& d = dst[g];
     const uint32_t B = c->geo.L.groups[g].block_tokens;
-    const uint64_t nreq = (static_cast<uint64_t>(n_hit) * C + B - 1) / B;
+    const uint64_t nreq = bsr::group_blocks(static_cast<uint64_t>(n_hit) * C, B);
     if (!d.block_table || !d.tensor_bases || !d.valid) return fail_with(BSR_E_ARG, "group %u: NULL destination pointer", g);
     if (d.n_blocks < nreq) return fail_with(BSR_E_ARG, "group %u: block table has %u blocks, prefix needs %llu", g, d.n_blocks, (unsigned long long)nreq);
     if (d.pool_blocks == 0) return fail_with(BSR_E_ARG, "group %u: pool_blocks is 0", g);
@@ -1499,9 +1504,8 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
       ig.div_p2 = bsr::pack_fastdiv(bsr::make_fastdiv((q.record_bytes - q.split_bytes) / 4));
     }
     fp.g[g] = bsr::GroupValid{d.block_table, d.valid, static_cast<uint32_t>(nreq), d.pool_blocks, B, 0};
-    total += static_cast<uint32_t>(nreq);
   }
-  fp.total_blocks = total;
+  fp.total_blocks = static_cast<uint32_t>(total);
   if (!trusted)
     if (int rc = check_tables(c, fp, total, compute)) return rc;
 

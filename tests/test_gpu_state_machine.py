@@ -176,3 +176,21 @@ def test_random_call_sequences(seed):
         assert seen["exposed"] >= 1 and seen["fallback"] >= 1 and seen["refused"] >= 1, seen
     finally:
         gc.close()
+
+
+@pytest.mark.parametrize("tokens", [1 << 29, (1 << 29) + 2048, (1 << 32) - 3])
+def test_more_block_table_entries_than_32_bits_are_refused(tokens):
+    """Eight groups of one-token blocks: what the prefix needs of their tables
+    is 2^32 entries or more.  Refused with the arguments, before any table is
+    read (the tables here are placeholders that nothing may touch)."""
+    layout = bsr.make_layout(1, [(1, 1, 4, bsr.BSR_KIND_CONTIG, 0)] * 8)
+    ctx = bsr.bsr_ctx_create(layout, 2, hip_device=0)
+    try:
+        say(f"case: eight tables of {tokens} entries")
+        word = torch.zeros(64, dtype=torch.int64, device="cuda")
+        dst = [bsr.group_dst(word.data_ptr(), word.data_ptr(), word.data_ptr(), tokens, 4)] * 8
+        with pytest.raises(bsr.BsrError) as e:
+            RestoreSession(ctx).bind(1, tokens, dst)
+        assert e.value.code == bsr.BSR_E_ARG and "block table entries" in str(e.value)
+    finally:
+        bsr.bsr_ctx_destroy(ctx)
