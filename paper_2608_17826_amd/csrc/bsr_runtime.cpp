@@ -1355,6 +1355,30 @@ static int check_table(uint32_t g, const int32_t* bt, uint32_t n, uint32_t pool_
   return BSR_OK;
 }
 
+// Whether a kernel may read `n` entries of every table: HIP knows the
+// allocation each lies in, and it reaches that far.  *all is false for memory
+// HIP does not know, which is left to the copies (and their own checks).
+static int tables_readable(const FinishParams& fp, bool* all) {
+  *all = true;
+  for (uint32_t g = 0; g < fp.n_groups; ++g) {
+    const uint64_t bytes = static_cast<uint64_t>(fp.g[g].n_req_blocks) * sizeof(int32_t);
+    if (!bytes) continue;
+    void* table = const_cast<int32_t*>(fp.g[g].block_table);
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, table) != hipSuccess || !base) {
+      (void)hipGetLastError();
+      *all = false;
+      continue;
+    }
+    const uint64_t at = static_cast<uint64_t>(static_cast<uint8_t*>(table) - static_cast<uint8_t*>(base));
+    if (at > size || bytes > size - at)
+      return fail_with(BSR_E_TRANSFER, "block table readback: group %u: %u entries reach past the table's allocation", g,
+                       fp.g[g].n_req_blocks);
+  }
+  return BSR_OK;
+}
+
 // Read the advertised part of every group's block table back once and check
 // it, behind what the compute stream holds.  The context lock is not held
 // while the device is waited for.
@@ -1362,7 +1386,9 @@ static int check_tables(bsr_ctx* c, const FinishParams& fp, uint64_t total, hipS
   if (total == 0) return BSR_OK;
   std::vector<uint8_t> seen;
   SessionRes* zone = nullptr;
-  if (total <= kTableEntries) {
+  bool readable = false;
+  if (int rc = tables_readable(fp, &readable)) return rc;
+  if (readable && total <= kTableEntries) {
     std::lock_guard<std::mutex> lk(c->mu);
     for (SessionRes& r : c->res)
       if (r.tables && !r.tables_busy) {

@@ -9,6 +9,7 @@ exposed with a pool image equal to the oracle's restore, or exposed not at
 all with its advertised blocks invalid (Prop. 2).
 """
 
+import ctypes
 import random
 
 import numpy as np
@@ -194,3 +195,28 @@ def test_more_block_table_entries_than_32_bits_are_refused(tokens):
         assert e.value.code == bsr.BSR_E_ARG and "block table entries" in str(e.value)
     finally:
         bsr.bsr_ctx_destroy(ctx)
+
+
+def test_block_table_past_its_allocation_is_refused():
+    """A table whose entries reach past the end of its device allocation is
+    refused at bind, before anything reads it."""
+    wi = generate(get_config(1))
+    gc = GpuCase(wi, W=2)
+    try:
+        n = gc.probe(3)[0]
+        need = oracle.request_blocks(n, wi.workload.chunk_tokens, wi.workload.groups[0].block_tokens)
+        path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+        room = torch.zeros(4 * need, dtype=torch.int32, device="cuda")
+        base, size = ctypes.c_void_p(), ctypes.c_size_t()
+        assert ctypes.CDLL(path).hipMemGetAddressRange(ctypes.byref(base), ctypes.byref(size),
+                                                       ctypes.c_void_p(room.data_ptr())) == 0
+        end = base.value + size.value
+        say(f"case: a table of {need} entries, {need - 1} of them inside its allocation")
+        d = gc.dsts()[0]
+        short = bsr.group_dst(end - 4 * (need - 1), d.tensor_bases, d.valid, need, d.pool_blocks)
+        with pytest.raises(bsr.BsrError) as e:
+            gc.session.bind(3, n, [short])
+        assert e.value.code == bsr.BSR_E_TRANSFER and "readback" in str(e.value)
+        assert gc.restore(3, n).exposed_tokens == n * wi.workload.chunk_tokens
+    finally:
+        gc.close()
