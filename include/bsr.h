@@ -66,7 +66,8 @@ extern "C" {
 #define BSR_MAX_GROUPS 8
 #define BSR_MAX_INSTALL_BATCH 32
 #define BSR_MAX_BOUND_REQUESTS 16 /* session slots of one context */
-#define BSR_STATIC_SCRATCH_BYTES (2u << 20) /* per-GPU scratch of bsr_ctx_create_static contexts */
+#define BSR_STATIC_SCRATCH_BYTES (2u << 20) /* per-GPU scratch of bsr_ctx_create_static contexts (and 2 KiB
+                                               beside it for the tag sums of direct installs) */
 #define BSR_NO_CHUNK 0xFFFFFFFFu
 
 /* status codes */

@@ -376,7 +376,9 @@ constexpr uint32_t kStageTileBytes = 16u * kStageThreads;
 // context's set-up with `device` current: the first claim on a device looks
 // the array's device address up (hipGetSymbolAddress) and keeps it; a claim
 // while another context of this process holds the device's array sets *busy.
-constexpr uint64_t kStaticScratchBytes = BSR_STATIC_SCRATCH_BYTES;
+// The direct installs' sums lie beside BSR_STATIC_SCRATCH_BYTES, which bounds
+// the partials and the rest of the verify words.
+constexpr uint64_t kStaticScratchBytes = BSR_STATIC_SCRATCH_BYTES + sizeof(VerifyAux::acc);
 constexpr int kMaxScratchDevices = 64;
 hipError_t static_scratch_claim(int device, void** ptr, bool* busy);
 void static_scratch_release(int device);

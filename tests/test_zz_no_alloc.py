@@ -143,3 +143,16 @@ def test_scratch_above_the_array_is_refused():
     ctx = bsr.bsr_ctx_create_static(layout, 32, hip_device=0, install_batch=8)   # 1.2 MB: fits
     bsr.bsr_ctx_destroy(ctx)
     assert w.n_full_chunks == 1
+
+
+def test_the_array_holds_partials_up_to_its_last_bytes():
+    """One-token chunks of many 4-byte tensors: one workgroup, two 8-byte tag
+    partials, per tensor.  131,056 of them are 2 MiB less 256 bytes, and the
+    verify words (192 bytes beside the direct installs' sums) fit behind them;
+    one more rounds up to the whole 2 MiB and is refused."""
+    def layout(n_tensors):
+        return bsr.make_layout(1, [(1, n_tensors, 4, bsr.BSR_KIND_CONTIG, 0)])
+    bsr.bsr_ctx_destroy(bsr.bsr_ctx_create_static(layout(131_056), 1, hip_device=0))
+    with pytest.raises(bsr.BsrError) as e:
+        bsr.bsr_ctx_create_static(layout(131_057), 1, hip_device=0)
+    assert e.value.code == bsr.BSR_E_ARG and "static array" in str(e.value)
