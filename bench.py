@@ -148,6 +148,7 @@ def main():
         t_r = time.perf_counter()
         out = sess.restore(rid, n, dsts)
         t_c = time.perf_counter()
+        out.stats["direct"] = bsr.bsr_direct_stats(ctx, rid)
         bsr.bsr_request_end(ctx, rid)
         assert out.fallback == 0 and out.exposed_tokens == n * w.chunk_tokens, out
         return n, out, t_c - t_r
@@ -171,11 +172,13 @@ def main():
         outs_k = [se.commit(r) for r, se in zip(rids, sessions)]
         t_c = time.perf_counter()
         for r, o, n_k in zip(rids, outs_k, ns):
+            o.stats["direct"] = bsr.bsr_direct_stats(ctx, r)
             bsr.bsr_request_end(ctx, r)
             assert o.fallback == 0 and o.exposed_tokens == n_k * w.chunk_tokens, o
         merged = outs_k[0]
         for key in ("n_install_launches", "install_ms_total", "installed_bytes"):
             merged.stats[key] = sum(o.stats[key] for o in outs_k)
+        merged.stats["direct"] = {key: sum(o.stats["direct"][key] for o in outs_k) for key in merged.stats["direct"]}
         merged.stats["peak_live_staging_bytes"] = sum(o.stats["peak_live_staging_bytes"] for o in outs_k)
         return ns[0], merged, t_c - t_r
 
@@ -199,12 +202,9 @@ def main():
     restored = K * n * chunk_payload
     value = restored * args.steps / elapsed / 1e9
     restore_only = restored * args.steps / sum(o[2] for o in outs) / 1e9
-    launches = sum(o[1].stats["n_install_launches"] for o in outs)
-    kern_ms = sum(o[1].stats["install_ms_total"] for o in outs)
-    installed = sum(o[1].stats["installed_bytes"] for o in outs)
-    avg_launch_ms = kern_ms / launches
-    bytes_per_launch = 2 * installed / launches        # read staged + write paged
-    achieved = bytes_per_launch / (avg_launch_ms * 1e-3) / 1e9
+    roofline, roofline_direct = install_rooflines([o[1].stats for o in outs], h2d)
+    if K > 1 and roofline_direct:
+        roofline_direct["note"] = f"per launch, while up to {K} requests' launches share the link"
     st = outs[-1][1].stats
 
     # The staging kernel's rate, from one more restore, untimed, with its
@@ -223,7 +223,13 @@ def main():
             b.copy_(a)
         torch.cuda.synchronize()
 
-    traffic, traffic_src, traffic_direct = recorded_traffic(w.name, st["install_batch"])
+    if roofline:
+        traffic, traffic_src, traffic_direct = recorded_traffic(w.name, st["install_batch"])
+        roofline.update({
+            "traffic": traffic, "traffic_source": traffic_src, "traffic_reads_counted_directly": traffic_direct,
+            "traffic_note": "HBM bytes per average launch of a 2,048-chunk restore: FETCH_SIZE and WRITE_SIZE "
+                            "scaled by a plain 1 GiB copy's readings; the other figure counts read requests "
+                            "by size (32/64/128 B) instead of scaling FETCH_SIZE"})
 
     sweep = None
     if args.concurrency_sweep and args.tier == "file":
@@ -302,17 +308,8 @@ def main():
             "requests": K,
             "profiling_subset": bool(args.held_chunks),
         },
-        "roofline": {
-            "bound": "hbm", "kernel": "k_install",
-            "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic, "traffic_source": traffic_src,
-            "traffic_reads_counted_directly": traffic_direct,
-            "traffic_note": "HBM bytes per average launch of a 2,048-chunk restore: FETCH_SIZE and WRITE_SIZE "
-                            "scaled by a plain 1 GiB copy's readings; the other figure counts read requests "
-                            "by size (32/64/128 B) instead of scaling FETCH_SIZE",
-            "bytes_per_launch": int(bytes_per_launch), "avg_launch_us": round(avg_launch_ms * 1e3, 2),
-            "launches_timed": launches,
-        },
+        "roofline": roofline or roofline_direct,
+        "roofline_direct": roofline_direct,
         "roofline_stage": None if not (stage_launches and stage_ms) else {
             "bound": "host link", "kernel": "k_stage",
             "achieved": round(stage_bytes / (stage_ms * 1e-3) / 1e9, 3), "peak": round(LINK_PEAK_GBPS, 3),
@@ -366,6 +363,33 @@ def main():
                              "concurrency_sweep": sweep}
     print(json.dumps(line), flush=True)
     bsr.bsr_ctx_destroy(ctx)
+
+
+def install_rooflines(stats, link_gbps):
+    """(k_install's record, k_install_direct's record) of the timed restores'
+    counters; None for a kernel that no launch ran.
+
+    k_install reads staged chunks from HBM and writes paged blocks there: its
+    bytes count twice, against HBM.  k_install_direct reads pinned memory over
+    the host link: its bytes count once, against the link.
+    """
+    def record(bound, kernel, launches, ms, nbytes, peak):
+        achieved = nbytes / (ms * 1e-3) / 1e9
+        return {"bound": bound, "kernel": kernel, "achieved": round(achieved, 1), "peak": round(peak, 3), "unit": "GB/s",
+                "frac": round(achieved / peak, 4), "bytes_per_launch": int(nbytes / launches),
+                "avg_launch_us": round(ms / launches * 1e3, 2), "launches_timed": launches}
+
+    d = {k: sum(s["direct"][k] for s in stats) for k in ("n_launches", "bytes", "ms_total")}
+    launches = sum(s["n_install_launches"] for s in stats) - d["n_launches"]
+    ms = sum(s["install_ms_total"] for s in stats) - d["ms_total"]
+    installed = sum(s["installed_bytes"] for s in stats) - d["bytes"]
+    ring = direct = None
+    if launches:
+        ring = record("hbm", "k_install", launches, ms, 2 * installed, HBM_PEAK_GBPS)
+    if d["n_launches"]:
+        direct = record("host link", "k_install_direct", d["n_launches"], d["ms_total"], d["bytes"], LINK_PEAK_GBPS)
+        direct["frac_of_measured_link"] = round(direct["achieved"] / link_gbps, 4)
+    return ring, direct
 
 
 def groups_alone(w, gs):

@@ -220,7 +220,7 @@ typedef struct bsr_stats {
   uint64_t request_id;
   uint32_t n_hit_chunks;        /* n: prefix length bound for restore */
   uint32_t window_chunks;       /* W */
-  uint32_t install_batch;       /* chunks per install launch, at most */
+  uint32_t install_batch;       /* chunks per install launch of chunks staged in the ring, at most */
   uint32_t n_windows;           /* restore_window calls accepted */
   uint32_t n_chunks_enqueued;   /* chunks whose copy and install were enqueued */
   uint32_t n_install_launches;
@@ -240,7 +240,7 @@ typedef struct bsr_stats {
   uint64_t enqueue_ns;             /* host time spent inside restore_window calls */
   uint64_t commit_wait_ns;         /* host time commit waited for the device */
   double install_ms_total;         /* sum of install-kernel durations (BSR_FLAG_TIME_INSTALL); with the
-                                      host link's time where they read pinned memory */
+                                      host link's time where they read pinned memory (bsr_direct_stats) */
   double install_ms_max;           /* longest install launch (BSR_FLAG_TIME_INSTALL) */
   uint64_t host_bounce_bytes;      /* pinned host landing zone of the file tier (when it served chunks) */
   uint32_t file_tier_chunks;       /* chunks restored from the file tier */
@@ -535,6 +535,15 @@ int bsr_stats_get(bsr_ctx* ctx, bsr_stats* out);
  * completion until bsr_request_end or its next probe.  BSR_E_NOTFOUND if
  * the request has neither. */
 int bsr_request_stats(bsr_ctx* ctx, uint64_t request_id, bsr_stats* out);
+
+/* The part of request_id's install counters that chunks installed straight
+ * from pinned memory account for (see BSR_FLAG_TWO_STREAMS): launches (in
+ * n_install_launches), payload bytes (in installed_bytes, read over the host
+ * link and never staged) and, once the request has completed, the sum of
+ * their durations (in install_ms_total; BSR_FLAG_TIME_INSTALL).  The rest of
+ * those counters is of launches that read the ring.  Any out-parameter may be
+ * NULL; the request as for bsr_request_stats. */
+int bsr_direct_stats(bsr_ctx* ctx, uint64_t request_id, uint32_t* n_launches, uint64_t* bytes, double* ms_total);
 
 /* Admission state: B, session slots, what is bound now and the peaks. */
 int bsr_admission_get(bsr_ctx* ctx, bsr_admission* out);

@@ -135,6 +135,7 @@ def _load() -> ct.CDLL:
         "bsr_request_end": (ct.c_int, [VP, U64]),
         "bsr_stats_get": (ct.c_int, [VP, P(bsr_stats)]),
         "bsr_request_stats": (ct.c_int, [VP, U64, P(bsr_stats)]),
+        "bsr_direct_stats": (ct.c_int, [VP, U64, P(U32), P(U64), P(ct.c_double)]),
         "bsr_admission_get": (ct.c_int, [VP, P(bsr_admission)]),
         "bsr_debug_inject": (ct.c_int, [VP, I32, U32, U32]),
         "bsr_measure_h2d": (ct.c_int, [VP, U64, U32, U32, P(ct.c_double)]),
@@ -373,6 +374,12 @@ def bsr_request_stats(ctx: Ctx, request_id: int) -> dict:
     s = bsr_stats()
     _check(_lib.bsr_request_stats(ctx, request_id, ct.byref(s)))
     return {name: getattr(s, name) for name, _ in bsr_stats._fields_}
+
+
+def bsr_direct_stats(ctx: Ctx, request_id: int) -> dict:
+    n, b, ms = ct.c_uint32(), ct.c_uint64(), ct.c_double()
+    _check(_lib.bsr_direct_stats(ctx, request_id, ct.byref(n), ct.byref(b), ct.byref(ms)))
+    return {"n_launches": n.value, "bytes": b.value, "ms_total": ms.value}
 
 
 def bsr_admission_get(ctx: Ctx) -> dict:

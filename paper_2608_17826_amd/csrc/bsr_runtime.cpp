@@ -418,6 +418,13 @@ constexpr uint8_t kTierPinned = 0;  // the pinned-host store
 constexpr uint8_t kTierFile = 1;    // the file-backed lower tier
 constexpr uint8_t kTierNone = 0xFF;
 
+// What direct installs account for in a request's install counters.
+struct DirectStats {
+  uint32_t launches = 0;
+  uint64_t bytes = 0;  // payload
+  double ms = 0;
+};
+
 struct Request {
   std::vector<uint64_t> keys;
   std::vector<uint8_t> tier;  // per chunk: the tier the probe found it in
@@ -426,6 +433,7 @@ struct Request {
   uint64_t probe_ns = 0;
   bool has_stats = false;  // counters of its last completion
   bsr_stats stats{};
+  DirectStats direct;
 };
 
 struct Inject {
@@ -490,7 +498,8 @@ struct Session {  // one bound request
   int64_t batch_seq = 0;
   uint32_t slots_touched = 0;
   std::vector<uint8_t> slot_used;
-  std::vector<std::pair<hipEvent_t, hipEvent_t>> timing;        // install launches
+  std::vector<std::pair<hipEvent_t, hipEvent_t>> timing;        // install launches out of the ring
+  std::vector<std::pair<hipEvent_t, hipEvent_t>> direct_timing; // ... and straight from pinned memory
   std::vector<std::pair<hipEvent_t, hipEvent_t>> stage_timing;  // staging-copy launches
   // chunks copied but not yet installed (the current install batch)
   std::vector<uint32_t> pend;
@@ -498,6 +507,7 @@ struct Session {  // one bound request
   std::vector<const uint8_t*> pend_src;  // their device-visible sources, when installed straight from pinned memory
   Inject inject;   // armed before this request was bound
   bsr_stats st{};  // this request's counters
+  DirectStats direct;
 };
 
 }  // namespace
@@ -716,7 +726,7 @@ int flush_batch(bsr_ctx* c, Session& s) {
     if (t1) c->timing_pool.push_back(t1);
     return rc;
   }
-  if (t0 && t1) s.timing.emplace_back(t0, t1);
+  if (t0 && t1) (direct ? s.direct_timing : s.timing).emplace_back(t0, t1);
   // The batch's slots are free once the install has read them: the verify
   // kernel reads only the tag partials, which the next install (later on
   // this stream) overwrites after it.  Releasing here keeps the verify off
@@ -740,6 +750,10 @@ int flush_batch(bsr_ctx* c, Session& s) {
   }
   s.st.n_install_launches++;
   s.st.installed_bytes += static_cast<uint64_t>(chunks.size()) * c->geo.chunk_payload;
+  if (direct) {
+    ++s.direct.launches;
+    s.direct.bytes += static_cast<uint64_t>(chunks.size()) * c->geo.chunk_payload;
+  }
   chunks.clear();
   tags.clear();
   s.pend_src.clear();
@@ -1066,7 +1080,7 @@ int bsr_ctx_destroy(bsr_ctx* c) {
       Session& s = kv.second;
       if (s.copy) (void)hipStreamSynchronize(s.copy);
       if (s.compute) (void)hipStreamSynchronize(s.compute);
-      for (auto* v : {&s.timing, &s.stage_timing})
+      for (auto* v : {&s.timing, &s.direct_timing, &s.stage_timing})
         for (auto& pr : *v) {
           (void)hipEventDestroy(pr.first);
           (void)hipEventDestroy(pr.second);
@@ -1642,7 +1656,7 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
   st.request_id = request_id;
   st.n_hit_chunks = n_hit;
   st.window_chunks = c->W;  // 0: whole-plan mode
-  st.install_batch = one_stream && s.batch_direct ? s.batch_direct : c->res.size() > 1 ? std::max(s.batch, s.batch_direct) : s.batch;
+  st.install_batch = s.batch;
   st.slot_bytes = c->geo.slot_bytes;
   st.staging_required_bytes = need;
   st.aux_device_bytes = c->aux_bytes;
@@ -2021,16 +2035,19 @@ static int complete_session(bsr_ctx* c, Session& s, std::unique_lock<std::mutex>
     if (fallback) *fallback = 1;
   }
   double tot = 0, mx = 0;
-  for (auto& pr : s.timing) {
-    float ms = 0;
-    if (hipEventElapsedTime(&ms, pr.first, pr.second) == hipSuccess) {
-      tot += ms;
-      mx = std::max(mx, static_cast<double>(ms));
+  for (auto* v : {&s.timing, &s.direct_timing}) {
+    for (auto& pr : *v) {
+      float ms = 0;
+      if (hipEventElapsedTime(&ms, pr.first, pr.second) == hipSuccess) {
+        tot += ms;
+        mx = std::max(mx, static_cast<double>(ms));
+        if (v == &s.direct_timing) s.direct.ms += ms;
+      }
+      c->timing_pool.push_back(pr.first);
+      c->timing_pool.push_back(pr.second);
     }
-    c->timing_pool.push_back(pr.first);
-    c->timing_pool.push_back(pr.second);
+    v->clear();
   }
-  s.timing.clear();
   st.install_ms_total = tot;
   st.install_ms_max = mx;
   double stot = 0;
@@ -2049,6 +2066,7 @@ static int complete_session(bsr_ctx* c, Session& s, std::unique_lock<std::mutex>
     it->second.phase = Phase::Done;
     it->second.has_stats = true;
     it->second.stats = st;
+    it->second.direct = s.direct;
   }
   c->last = st;
   c->last_id = id;
@@ -2185,6 +2203,24 @@ int bsr_request_stats(bsr_ctx* c, uint64_t request_id, bsr_stats* out) {
   if (it == c->requests.end() || !it->second.has_stats)
     return fail_with(BSR_E_NOTFOUND, "no counters for request %llu", (unsigned long long)request_id);
   *out = it->second.stats;
+  return BSR_OK;
+}
+
+int bsr_direct_stats(bsr_ctx* c, uint64_t request_id, uint32_t* n_launches, uint64_t* bytes, double* ms_total) {
+  if (!c) return fail_with(BSR_E_ARG, "ctx is NULL");
+  std::lock_guard<std::mutex> lk(c->mu);
+  DirectStats d;
+  if (const Session* s = find_bound(c, request_id)) {
+    d = s->direct;
+  } else {
+    auto it = c->requests.find(request_id);
+    if (it == c->requests.end() || !it->second.has_stats)
+      return fail_with(BSR_E_NOTFOUND, "no counters for request %llu", (unsigned long long)request_id);
+    d = it->second.direct;
+  }
+  if (n_launches) *n_launches = d.launches;
+  if (bytes) *bytes = d.bytes;
+  if (ms_total) *ms_total = d.ms;
   return BSR_OK;
 }
 

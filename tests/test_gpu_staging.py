@@ -276,13 +276,21 @@ def test_direct_and_staged_chunks_in_one_request(tmp_path):
     case, n, res = _oracle(wi, 6)
     pinned = [i for i in range(40) if (i // 3) % 2 or i > 33]
     say("case: 40 chunks, three pinned, three in files, and so on, W=6")
-    gc = GpuCase(wi, W=6, pinned_chunks=pinned)
+    gc = GpuCase(wi, W=6, pinned_chunks=pinned, flags=bsr.BSR_FLAG_TIME_INSTALL)
     try:
         gc.put_files(str(tmp_path), [i for i in range(40) if i not in pinned])
         assert gc.probe(8)[0] == n == 40
         out = gc.restore(8, n)
         _check(wi, case, res, out, gc.dev.pools, gc.dev.valid)
         assert out.stats["file_tier_chunks"] == 40 - len(pinned) == out.stats["n_stage_launches"]
+        assert out.stats["install_batch"] == 6      # of the ring's launches
+        d = bsr.bsr_direct_stats(gc.ctx, 8)
+        assert 0 < d["n_launches"] < out.stats["n_install_launches"] and 0 < d["ms_total"] < out.stats["install_ms_total"]
+        assert d["bytes"] * 40 == len(pinned) * out.stats["installed_bytes"]
+        assert gc.probe(9)[0] == n
+        with pytest.raises(bsr.BsrError) as e:
+            bsr.bsr_direct_stats(gc.ctx, 9)         # probed only
+        assert e.value.code == bsr.BSR_E_NOTFOUND
     finally:
         gc.close()
 
