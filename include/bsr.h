@@ -471,7 +471,12 @@ int bsr_request_bind(bsr_ctx* ctx, uint64_t request_id, uint32_t n_hit_chunks,
  * commit, invalidate, mark, end -- installs them first) it enqueues the
  * install kernel on compute_stream, releases the batch's slots behind it,
  * then enqueues the verify kernel (which reads only the install's tag
- * partials, not the slots).  On a
+ * partials, not the slots).  Chunks installed straight from pinned memory
+ * have no copy of their own: when the call returns, the transfer of up to
+ * 1 MiB of them, and of up to 64 MiB while an earlier launch of theirs is
+ * still running, may not have been enqueued; the next call of the request
+ * enqueues it, alone or with its own chunks (install_batch bounds such
+ * launches from above only).  On a
  * host-detected failure it enqueues the chunks before the failing one, then
  * an invalidate, and returns BSR_E_MISSING / BSR_E_TIMEOUT /
  * BSR_E_TRANSFER; later windows return BSR_E_STATE.  Device-detected

@@ -234,8 +234,9 @@ struct DirectParams {
   const uint8_t* src[BSR_MAX_INSTALL_BATCH];
   bsr_dev_status* status;
   VerifyAux* aux;
+  uint32_t* done;      // in pinned host memory: gets `ticket` as the launch ends; may be null
+  uint32_t ticket;
   uint32_t stretches;  // set by the launch: each workgroup takes consecutive pieces
-  uint32_t pad;
   uint64_t expected[BSR_MAX_INSTALL_BATCH][BSR_MAX_GROUPS];  // stored tags
 };
 // Its grid: workgroups that take pieces in turn, each with two in flight, as

@@ -87,11 +87,14 @@ constexpr uint64_t kDirectBytes = 768ull << 20;
 // 1K-token workload (295 KB windows) takes 132 us with a launch per window,
 // 111 with 512 KiB, 96 with 1 MiB and 99 in one launch, which starts late.
 constexpr uint64_t kDirectFlushBytes = 1ull << 20;
-// Chunks that hold less than the request has launched so far wait for the next
-// window too, up to this many bytes: the launches of many small windows double
-// in size, each about as long as the device still has work before it, and a
-// caller that pauses between windows leaves at most 1.2 ms of link time to
-// the last of them.  Measured in turn, a launch per window and so: 155 MB in
+// While the launch before is still running, chunks that hold less than the
+// request has launched so far wait for the next window too, up to this many
+// bytes: the launches of many small windows double in size, each about as long
+// as the device still has work before it.  A window that ends with that launch
+// done is launched whatever it holds (from kDirectFlushBytes on), so a caller
+// that pauses between windows leaves the link idle for the part of its pause
+// that the device outlasts, with at most 1.2 ms of link time waiting.
+// Measured in turn, a launch per window and so: 155 MB in
 // 1.2 MB windows 3,735 and 2,882 us, 295 MB in 4.9 MB windows 6,018 and 5,474,
 // 55 MB in 707 KB windows 1,710 and 1,579, 513 MB in 131 MB windows the same.
 constexpr uint64_t kDirectHoldBytes = 64ull << 20;
@@ -105,7 +108,8 @@ constexpr uint64_t kSerpentineBytes = 256ull << 20;
 // Block table entries that one bind reads back through a session slot's
 // landing zone (64 KiB); larger tables are copied, 16-20 us a group.
 constexpr uint64_t kTableEntries = 16384;
-constexpr uint64_t kTablesOffset = 256;  // behind the status mirror
+constexpr uint64_t kDoneOffset = 128;    // behind the status mirror: the last direct launch that has ended
+constexpr uint64_t kTablesOffset = 256;
 constexpr uint64_t kHostBytes = kTablesOffset + (kTableEntries + 1) * sizeof(int32_t);
 constexpr uint64_t kSpinNs = 100000;  // a bind polls this long before it waits for its stream
 constexpr uint32_t kTimingFlags = BSR_FLAG_TIME_INSTALL | BSR_FLAG_TIME_STAGE;
@@ -456,6 +460,11 @@ struct SessionRes {
   int32_t* tables_dev = nullptr;
   uint32_t table_ticket = 0;
   bool tables_busy = false;
+  // The ticket of the last direct launch that has ended, in the same
+  // allocation, and that of the last one that reports it; null: not known.
+  uint32_t* direct_done = nullptr;
+  uint32_t* direct_done_dev = nullptr;
+  uint32_t direct_ticket = 0;
   std::vector<hipEvent_t> full_ev, free_ev;
   bool in_use = false;
   // A context that allocates nothing: partials and verify words are in the
@@ -715,8 +724,11 @@ int flush_batch(bsr_ctx* c, Session& s) {
     std::copy(s.pend_src.begin(), s.pend_src.end(), dp.src);
     dp.status = s.status;
     dp.aux = r.verify_aux;
+    if (chunks.back() + 1 < s.n_hit) dp.done = r.direct_done_dev;  // asked for only while chunks are left
+    dp.ticket = r.direct_ticket + 1;
     for (size_t i = 0; i < chunks.size(); ++i) std::copy(tags[i].begin(), tags[i].end(), dp.expected[i]);
     launched = bsr::launch_install_direct(dp, s.compute, t0, t1);
+    if (launched == hipSuccess && dp.done) r.direct_ticket = dp.ticket;
     s.direct_bytes += static_cast<uint64_t>(ip.h.n_chunks) * c->geo.slot_bytes;
   } else {
     launched = bsr::launch_install(ip, ip.h.n_chunks * ip.h.wg_per_chunk, s.compute, t0, t1);
@@ -1044,6 +1056,9 @@ static int ctx_create(const bsr_layout* layout, const bsr_config* config, bsr_ct
           r.tables = reinterpret_cast<int32_t*>(reinterpret_cast<uint8_t*>(r.host_status) + kTablesOffset);
           r.tables_dev = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(dv) + kTablesOffset);
           r.tables[kTableEntries] = 0;  // the flag: no ticket yet
+          r.direct_done = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(r.host_status) + kDoneOffset);
+          r.direct_done_dev = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(dv) + kDoneOffset);
+          *r.direct_done = r.direct_ticket;  // nothing in flight
         } else {
           (void)hipGetLastError();
         }
@@ -1932,8 +1947,11 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
       if ((rc = flush_all())) return rc;
   }
   if (hipError_t e = issue_runs(&done)) return fail_runs(e, done);  // nothing of this call stays unstaged
-  const uint64_t least = std::max(kDirectFlushBytes, std::min(s.direct_bytes, kDirectHoldBytes));
-  const bool enough = !c->cfg.install_batch && s.pend_src.size() * c->geo.slot_bytes >= least;
+  // direct chunks wait for the next window only while they are few, or while
+  // the device is busy with the launch before and they hold less than that
+  const uint64_t pend_bytes = s.pend_src.size() * c->geo.slot_bytes;
+  const bool idle = !res.direct_done || __atomic_load_n(res.direct_done, __ATOMIC_RELAXED) == res.direct_ticket;
+  const bool enough = pend_bytes >= kDirectFlushBytes && (idle || pend_bytes >= std::min(s.direct_bytes, kDirectHoldBytes));
   if (first_chunk + n_chunks == s.n_hit || enough)
     if ((rc = flush_batch(c, s))) return launch_failed(c, s, rc);  // the prefix is complete
   s.next_chunk = first_chunk + n_chunks;

@@ -348,3 +348,37 @@ def test_bind_checks_the_last_block_id(n_chunks):
         _check(wi, case, res, gc.restore(9, n), gc.dev.pools, gc.dev.valid)
     finally:
         gc.close()
+
+
+@pytest.mark.parametrize("batch", [0, 8])
+@pytest.mark.parametrize("paused", [True, False])
+def test_direct_chunks_wait_only_while_the_device_is_busy(batch, paused):
+    """Windows of two 1 MiB chunks.  A caller that lets the device finish
+    between windows has every window launched by its own call, whatever
+    install_batch allows; while the device is busy (a spin kernel ahead on the
+    compute stream) launches double: the third window waits for the fourth,
+    the fifth for the last."""
+    w = _direct_workload([(64, 4, 1024, 0)], 256, 12, 8)
+    wi = generate(w)
+    case, n, res = _oracle(wi, 8)
+    say(f"case: 12 chunks of 1 MiB in windows of 2, install_batch {batch}, {'paused' if paused else 'busy'}")
+    gc = GpuCase(wi, W=8, install_batch=batch)
+    launches = []
+    try:
+        assert gc.probe(8)[0] == n == 12
+
+        def busy():
+            if not paused:
+                with torch.cuda.stream(gc.session.compute_stream):
+                    torch.cuda._sleep(100_000_000)  # far longer than the calls take
+
+        def after(j):
+            launches.append(bsr.bsr_request_stats(gc.ctx, 8)["n_install_launches"])
+            if paused:
+                gc.session.compute_stream.synchronize()
+                gc.session.copy_stream.synchronize()
+        out = gc.restore(8, n, plan=[(i, 2) for i in range(0, 12, 2)], after_bind=busy, after_window=after)
+        _check(wi, case, res, out, gc.dev.pools, gc.dev.valid)
+        assert launches == ([1, 2, 3, 4, 5, 6] if paused else [1, 2, 2, 3, 3, 4])
+    finally:
+        gc.close()
