@@ -114,10 +114,13 @@ extern "C" {
                                       order, not events between the two streams, orders its copies,
                                       installs and slot reuse; its chunks in a pinned arena are installed
                                       straight from there, with no staging copy (each still counts as one
-                                      live slot of the ring, which is provided as for any request).  So is
-                                      a request of at most 768 MiB, all of it in a pinned arena, of a context
-                                      without a staging budget, and any chunk in a pinned arena while more
-                                      than one request is bound */
+                                      live slot of the ring, which is provided as for any request).  So
+                                      are, but by launches on the copy stream, those of a request of at most
+                                      768 MiB, all of it in a pinned arena, of a context without a staging
+                                      budget, and any chunk in a pinned arena while more than one request is
+                                      bound.  Each such launch comes after what the compute stream held when
+                                      it was enqueued; the compute stream waits for them where the last
+                                      window ends, and before a commit, mark or invalidate */
 #define BSR_FLAG_SDMA_COPIES 4u   /* stage chunks with the copy engine (hipMemcpyAsync) instead of the
                                       library's staging-copy kernel.  By default a small kernel on the copy
                                       stream reads each run of chunks from pinned host memory (the library's
@@ -204,7 +207,8 @@ typedef struct bsr_group_dst {
 
 /* Request status word block, device-resident and caller-allocated (64 bytes).
  * Written only by the library's kernels, in stream order on the compute
- * stream.  exposed_tokens is non-zero only after a successful commit. */
+ * stream (and by installs on the copy stream, see BSR_FLAG_TWO_STREAMS, which
+ * that stream waits for before it writes them again).  exposed_tokens is non-zero only after a successful commit. */
 typedef struct bsr_dev_status {
   uint32_t fail;               /* BSR_FAIL_* of the first failure, 0 = none */
   uint32_t first_failed_chunk; /* chunk index of the first failure, BSR_NO_CHUNK = none */

@@ -70,8 +70,8 @@ constexpr uint64_t kAlign = 256;
 // from pinned memory.
 constexpr uint64_t kOneStreamBytes = 64ull << 20;
 // Requests of at most this many chunk bytes, all of them in the pinned store,
-// are installed straight from there on the compute stream when no other
-// request can be bound beside them (no staging budget): the link is loaded from
+// are installed straight from there when no other request can be bound beside
+// them (no staging budget): the link is loaded from
 // the first chunk to the last, where the ring's pipeline has its first copy and
 // its last install to itself, hands over between two streams at every batch and
 // loses link rate to the installs beside its copies.  Measured in turn, ring
@@ -466,6 +466,9 @@ struct SessionRes {
   uint32_t* direct_done_dev = nullptr;
   uint32_t direct_ticket = 0;
   std::vector<hipEvent_t> full_ev, free_ev;
+  // direct launches on the copy stream: the compute stream's work before one,
+  // and theirs before the compute stream's next kernel
+  hipEvent_t compute_ev = nullptr, copy_ev = nullptr;
   bool in_use = false;
   // A context that allocates nothing: partials and verify words are in the
   // library's static array, and the status mirror is status_buf (plain host
@@ -488,10 +491,14 @@ struct Session {  // one bound request
   // without their hand-over latency.
   bool one_stream = false;
   uint32_t batch = 0;       // chunks per install launch
-  // Chunks per install launch that reads pinned memory itself (requests on
-  // one stream, and any request while it shares the link); 0: every chunk goes
-  // through the ring.
+  // Chunks per install launch that reads pinned memory itself; 0: every chunk
+  // goes through the ring.
   uint32_t batch_direct = 0;
+  // Its chunks in the pinned store are installed straight from there; any
+  // other request's only while it shares the link.
+  bool direct_alone = false;
+  bool fence_due = false;     // the copy stream has not yet come after bind's compute-stream work
+  bool direct_dirty = false;  // direct launches on the copy stream that no compute-stream wait covers yet
   uint64_t direct_bytes = 0;  // launched with no ring in between
   bool copy_dirty = false;  // the copy stream holds work no compute-stream wait covers yet
   uint32_t time_flags = 0;  // BSR_FLAG_TIME_INSTALL / BSR_FLAG_TIME_STAGE, taken at bind
@@ -607,6 +614,15 @@ struct Run {
   uint32_t first = 0, count = 0;
 };
 
+// The copy stream waits for what the compute stream holds.
+hipError_t fence_copy(bsr_ctx* c, Session& s) {
+  SessionRes& r = c->res[s.res];
+  hipError_t e = hipEventRecord(r.compute_ev, s.compute);
+  if (e == hipSuccess) e = hipStreamWaitEvent(s.copy, r.compute_ev, 0);
+  if (e == hipSuccess) s.fence_due = false;
+  return e;
+}
+
 // Staging copies of `n` runs (at most kStageMaxRuns) from host memory into
 // the ring, on the copy stream; *done is the runs enqueued, all n on success.
 // When the sources lie in a pinned allocation [base, base + extent) whose
@@ -617,6 +633,8 @@ struct Run {
 hipError_t stage_copy(bsr_ctx* c, Session& s, const Run* runs, uint32_t n, const uint8_t* base, const uint8_t* dev,
                       uint64_t extent, uint32_t* done) {
   *done = 0;
+  if (s.fence_due)
+    if (hipError_t e = fence_copy(c, s)) return e;
   s.copy_dirty = true;
   // With several requests bound, each staging on a copy stream of its own
   // (BSR_FLAG_TWO_STREAMS, or chunks of the file tier), their k_stage launches
@@ -665,6 +683,26 @@ hipError_t stage_copy(bsr_ctx* c, Session& s, const Run* runs, uint32_t n, const
   return hipSuccess;
 }
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
+// Nothing is left to run on the stream.  (A capture's work is still to come.)
+bool stream_idle(hipStream_t st) {
+  if (capturing(st)) return false;
+  if (hipStreamQuery(st) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+// No direct launch of the slot that reports its end is still running (true if none can).
+bool direct_idle(const SessionRes& r) {
+  return !r.direct_done || __atomic_load_n(r.direct_done, __ATOMIC_RELAXED) == r.direct_ticket;
+}
+
 // Enqueue install + verify for the chunks staged since the last flush.
 int flush_batch(bsr_ctx* c, Session& s) {
   std::vector<uint32_t>& chunks = s.pend;
@@ -691,7 +729,7 @@ int flush_batch(bsr_ctx* c, Session& s) {
   if (events) {
     if ((rc = hip_check(hipEventRecord(full, s.copy), "hipEventRecord(full)"))) return rc;
     if ((rc = hip_check(hipStreamWaitEvent(s.compute, full, 0), "hipStreamWaitEvent(full)"))) return rc;
-    s.copy_dirty = false;
+    s.copy_dirty = s.direct_dirty = false;
   }
 
   // the kernel takes chunk first_chunk + c to slot first_slot + c, less W
@@ -700,6 +738,22 @@ int flush_batch(bsr_ctx* c, Session& s) {
   if ((!direct && chunks.size() > s.window) || chunks.back() - chunks.front() + 1 != chunks.size() ||
       (direct && s.pend_src.size() != chunks.size()))
     return fail_with(BSR_E_STATE, "install batch of %zu chunks is not a run of at most W = %u", chunks.size(), s.window);
+  // The first direct launch of a request follows the begin kernel on the
+  // compute stream.  Later ones leave that stream to the caller's work: they
+  // come after what it holds now (kernels of ours, and the caller's own on the
+  // destination), as an install on it would, but what is queued there later
+  // does not wait for them.  A hand-over costs some 17 us of host time and
+  // 10 us of the device: 75 MB in three launches take 1,367 us all on the
+  // compute stream, 1,384 so, and 1,420 with the first on the copy stream and
+  // the commit back on the compute stream (complete_session).
+  const hipStream_t on = direct && s.direct.launches ? s.copy : s.compute;
+  if (on != s.compute) {
+    const bool behind_first = !s.direct_dirty && !direct_idle(r);
+    if (behind_first || !stream_idle(s.compute))
+      if ((rc = hip_check(fence_copy(c, s), "copy stream behind the compute stream"))) return rc;
+    s.fence_due = false;
+    s.direct_dirty = true;
+  }
   InstallParams ip = s.ip;
   ip.h.n_chunks = static_cast<uint32_t>(chunks.size());
   ip.h.first_chunk = chunks.front();
@@ -727,7 +781,7 @@ int flush_batch(bsr_ctx* c, Session& s) {
     if (chunks.back() + 1 < s.n_hit) dp.done = r.direct_done_dev;  // asked for only while chunks are left
     dp.ticket = r.direct_ticket + 1;
     for (size_t i = 0; i < chunks.size(); ++i) std::copy(tags[i].begin(), tags[i].end(), dp.expected[i]);
-    launched = bsr::launch_install_direct(dp, s.compute, t0, t1);
+    launched = bsr::launch_install_direct(dp, on, t0, t1);
     if (launched == hipSuccess && dp.done) r.direct_ticket = dp.ticket;
     s.direct_bytes += static_cast<uint64_t>(ip.h.n_chunks) * c->geo.slot_bytes;
   } else {
@@ -772,16 +826,31 @@ int flush_batch(bsr_ctx* c, Session& s) {
   return BSR_OK;
 }
 
-int enqueue_finish(bsr_ctx* c, Session& s, uint32_t mode, uint32_t reason, uint32_t chunk, uint32_t mask) {
-  // chunks still waiting for their install go first (stream order)
-  if (int rc = flush_batch(c, s)) return rc;
+// The compute stream waits for the direct launches on the copy stream.
+int join_direct(bsr_ctx* c, Session& s) {
+  if (!s.direct_dirty) return BSR_OK;
+  SessionRes& r = c->res[s.res];
+  if (int rc = hip_check(hipEventRecord(r.copy_ev, s.copy), "hipEventRecord(copy)")) return rc;
+  if (int rc = hip_check(hipStreamWaitEvent(s.compute, r.copy_ev, 0), "hipStreamWaitEvent(copy)")) return rc;
+  s.copy_dirty = s.direct_dirty = false;
+  return BSR_OK;
+}
+
+int launch_mode(bsr_ctx* c, Session& s, uint32_t mode, uint32_t reason, uint32_t chunk, uint32_t mask, hipStream_t on) {
   FinishParams fp = s.fp;
   fp.mode = mode;
   fp.reason = reason;
   fp.chunk = chunk;
   fp.group_mask = mask;
   fp.mirror = mode == bsr::kFinishCommit ? c->res[s.res].mirror_dev : nullptr;
-  return hip_check(bsr::launch_finish(fp, s.compute), "finish launch");
+  return hip_check(bsr::launch_finish(fp, on), "finish launch");
+}
+
+int enqueue_finish(bsr_ctx* c, Session& s, uint32_t mode, uint32_t reason, uint32_t chunk, uint32_t mask) {
+  // chunks still waiting for their install go first (stream order)
+  if (int rc = flush_batch(c, s)) return rc;
+  if (int rc = join_direct(c, s)) return rc;
+  return launch_mode(c, s, mode, reason, chunk, mask, s.compute);
 }
 
 // A launch or enqueue failed: the device may not hold what the host
@@ -872,6 +941,10 @@ static void free_session_res(SessionRes& r) {
     if (e) (void)hipEventDestroy(e);
   r.full_ev.clear();
   r.free_ev.clear();
+  for (hipEvent_t* e : {&r.compute_ev, &r.copy_ev}) {
+    if (*e) (void)hipEventDestroy(*e);
+    *e = nullptr;
+  }
   if (!r.static_scratch) {
     if (r.partials) (void)hipFree(r.partials);
     if (r.verify_aux) (void)hipFree(r.verify_aux);
@@ -1066,6 +1139,8 @@ static int ctx_create(const bsr_layout* layout, const bsr_config* config, bsr_ct
       for (uint32_t i = 0; ok && i < E; ++i)
         ok = hipEventCreateWithFlags(&r.full_ev[i], hipEventDisableTiming) == hipSuccess &&
              hipEventCreateWithFlags(&r.free_ev[i], hipEventDisableTiming) == hipSuccess;
+      ok = ok && hipEventCreateWithFlags(&r.compute_ev, hipEventDisableTiming) == hipSuccess &&
+           hipEventCreateWithFlags(&r.copy_ev, hipEventDisableTiming) == hipSuccess;
     }
     if (!ok) {
       bsr_ctx_destroy(c);
@@ -1618,22 +1693,27 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
     check.mode = bsr::kFinishCheckTables;
     if (int rc = hip_check(bsr::launch_finish(check, compute), "block table check launch")) return rc;
   }
-  // A request of at most kOneStreamBytes of chunks is staged on the compute
+  // A request of at most kOneStreamBytes of chunks stays on the compute
   // stream: its copies and installs are short, and the hand-over between two
   // streams (an event recorded on one, waited for on the other) costs about
-  // as much as they do.  One that needs no staging stays there up to
-  // kDirectBytes; chunks of the file tier go through the ring, and their
-  // copies need a stream beside the installs.  A larger request, or one under a
-  // staging budget, is installed straight from pinned memory while it shares
-  // the link (bsr_restore_window).
+  // as much as they do.  A larger one leaves that stream to the caller's own
+  // work while its transfers run, through the ring or straight from pinned
+  // memory (flush_batch).  Measured with 1.35 ms of other kernels queued there
+  // after each of eight windows of 78 MB (1.36 ms of link): 12.4 ms so, 13.6
+  // through the ring on two streams, 21.8 with the direct launches on the
+  // compute stream.
   const bool two_streams = (c->cfg.flags & BSR_FLAG_TWO_STREAMS) != 0;
   const bool can_direct = !two_streams && c->kernel_copies && c->store.arena_dev;
-  const bool all_direct = can_direct && c->res.size() == 1 &&
-                          std::all_of(rq.tier.begin(), rq.tier.begin() + n_hit, [](uint8_t t) { return t == kTierPinned; });
-  const bool one_stream = !two_streams && static_cast<uint64_t>(n_hit) * c->geo.slot_bytes <=
-                                              (all_direct ? kDirectBytes : kOneStreamBytes);
-  // no copy of this request may overwrite the ring before earlier compute work is done
-  if (!one_stream) {
+  const uint64_t chunk_bytes = static_cast<uint64_t>(n_hit) * c->geo.slot_bytes;
+  const bool one_stream = !two_streams && chunk_bytes <= kOneStreamBytes;
+  const bool direct_alone = can_direct && (one_stream ||
+      (c->res.size() == 1 && chunk_bytes <= kDirectBytes &&
+       std::all_of(rq.tier.begin(), rq.tier.begin() + n_hit, [](uint8_t t) { return t == kTierPinned; })));
+  // no copy of this request may overwrite the ring before earlier compute work
+  // is done; one that is installed straight from pinned memory has no copies,
+  // and its launches see to that themselves
+  const bool fence_due = direct_alone && !one_stream;
+  if (!one_stream && !fence_due) {
     if (int rc = hip_check(hipEventRecord(res.free_ev[0], compute), "hipEventRecord")) return rc;
     if (int rc = hip_check(hipStreamWaitEvent(copy, res.free_ev[0], 0), "hipStreamWaitEvent")) return rc;
   }
@@ -1650,6 +1730,8 @@ int bsr_request_bind(bsr_ctx* c, uint64_t request_id, uint32_t n_hit, const bsr_
   s.time_flags = c->cfg.flags & kTimingFlags;
   s.batch = one_stream ? c->batch_one : c->batch;
   s.batch_direct = can_direct ? c->batch_direct : 0;
+  s.direct_alone = direct_alone;
+  s.fence_due = fence_due;
   s.copy = one_stream ? compute : copy;
   s.compute = compute;
   s.ip = ip;
@@ -1871,8 +1953,8 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
     // ring never share a launch
     // Sharing the link, a request is installed straight from pinned memory
     // whatever its size: two requests of 310 MB, W = 8, take 14.2 ms through
-    // the copy engine and 11.0 so (44 and 56 GB/s in aggregate).
-    const bool direct = s.batch_direct && !from_file && src_block && (s.one_stream || c->bound.size() > 1);
+    // the copy engine and 11.2 so (44 and 56 GB/s in aggregate).
+    const bool direct = s.batch_direct && !from_file && src_block && (s.direct_alone || c->bound.size() > 1);
     if (direct == s.pend_src.empty() && !batch.empty())
       if ((rc = flush_all())) return rc;
     if (direct) {
@@ -1950,10 +2032,12 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
   // direct chunks wait for the next window only while they are few, or while
   // the device is busy with the launch before and they hold less than that
   const uint64_t pend_bytes = s.pend_src.size() * c->geo.slot_bytes;
-  const bool idle = !res.direct_done || __atomic_load_n(res.direct_done, __ATOMIC_RELAXED) == res.direct_ticket;
-  const bool enough = pend_bytes >= kDirectFlushBytes && (idle || pend_bytes >= std::min(s.direct_bytes, kDirectHoldBytes));
-  if (first_chunk + n_chunks == s.n_hit || enough)
-    if ((rc = flush_batch(c, s))) return launch_failed(c, s, rc);  // the prefix is complete
+  const bool enough = pend_bytes >= kDirectFlushBytes && (direct_idle(res) || pend_bytes >= std::min(s.direct_bytes, kDirectHoldBytes));
+  const bool complete = first_chunk + n_chunks == s.n_hit;
+  if (complete || enough)
+    if ((rc = flush_batch(c, s))) return launch_failed(c, s, rc);
+  if (complete && capturing(s.compute))  // a capture must end with its streams joined
+    if ((rc = join_direct(c, s))) return launch_failed(c, s, rc);
   s.next_chunk = first_chunk + n_chunks;
   ++s.st.n_windows;
   s.st.peak_live_staging_bytes = static_cast<uint64_t>(s.slots_touched) * c->geo.slot_bytes;
@@ -2006,6 +2090,7 @@ static int complete_session(bsr_ctx* c, Session& s, std::unique_lock<std::mutex>
   SessionRes& res = c->res[s.res];
   bsr_stats& st = s.st;
   int rc = BSR_OK;
+  bool late = false;  // the commit kernel runs on the copy stream
   if (run_commit) {
     if (s.failed || s.next_chunk < s.n_hit) {
       // a failure the host knows of, or an incomplete prefix, is never
@@ -2015,18 +2100,30 @@ static int complete_session(bsr_ctx* c, Session& s, std::unique_lock<std::mutex>
       rc = enqueue_finish(c, s, bsr::kFinishInvalidate, static_cast<uint32_t>(reason), BSR_NO_CHUNK, 0);
       s.failed = true;
     }
-    if (!rc) rc = enqueue_finish(c, s, bsr::kFinishCommit, 0, BSR_NO_CHUNK, 0);
+    if (!rc) rc = flush_batch(c, s);
+    // behind direct launches on the copy stream the commit goes there too, once
+    // the compute stream is done: no hand-over after the last of them
+    late = !rc && s.direct_dirty;
+    if (!rc && !late) rc = enqueue_finish(c, s, bsr::kFinishCommit, 0, BSR_NO_CHUNK, 0);
   }
-  if (!rc) rc = flush_batch(c, s);
-  if (!rc && !(run_commit && res.mirror_dev))  // else the commit kernel has written the mirror
-    rc = hip_check(hipMemcpyAsync(res.host_status, s.status, sizeof(bsr_dev_status), hipMemcpyDeviceToHost, s.compute), "status readback");
+  if (!rc && !late) rc = flush_batch(c, s);
+  if (!rc && !late) rc = join_direct(c, s);
   s.completing = true;
   const hipStream_t compute = s.compute, copy = s.copy;
+  const uint64_t t0 = now_ns();
+  if (late) {
+    lk.unlock();
+    rc = hip_check(hipStreamSynchronize(compute), "hipStreamSynchronize(compute)");
+    lk.lock();
+    if (!rc) rc = launch_mode(c, s, bsr::kFinishCommit, 0, BSR_NO_CHUNK, 0, copy);
+  }
+  if (!rc && !(run_commit && res.mirror_dev))  // else the commit kernel has written the mirror
+    rc = hip_check(hipMemcpyAsync(res.host_status, s.status, sizeof(bsr_dev_status), hipMemcpyDeviceToHost, late ? copy : compute), "status readback");
   // Once the compute stream has waited for the last copy event, every copy
   // is behind its sync; the copy stream is synchronised only if it holds
-  // work recorded after that (a run whose batch was never installed).
-  const bool sync_copy = copy != compute && s.copy_dirty;
-  const uint64_t t0 = now_ns();
+  // work recorded after that (a run whose batch was never installed, or a late
+  // commit).
+  const bool sync_copy = copy != compute && (s.copy_dirty || s.direct_dirty);
   lk.unlock();
   int rc2 = hip_check(hipStreamSynchronize(compute), "hipStreamSynchronize(compute)");
   int rc3 = sync_copy ? hip_check(hipStreamSynchronize(copy), "hipStreamSynchronize(copy)") : BSR_OK;

@@ -36,9 +36,9 @@ pytestmark = [pytest.mark.gpu, pytest.mark.timeout(600)]
 adm = oracle.admission
 
 
-def _variant(k, index, n_tokens=None):
+def _variant(k, index, n_tokens=None, **kw):
     w = get_config(k)
-    kw = {"index": index}
+    kw["index"] = index
     if n_tokens:
         kw["n_tokens"] = n_tokens
     return generate(dataclasses.replace(w, **kw))
@@ -488,5 +488,80 @@ def test_file_tier_requests_share_the_bounce_pool(tmp_path):
             t.commit()
             t.check_success()
             assert t.out.stats["file_tier_chunks"] == 16
+    finally:
+        bsr.bsr_ctx_destroy(ctx)
+
+
+def _concurrent_session(gc):
+    """A session whose two streams run side by side: streams share a few
+    hardware queues, and two on one queue would follow each other."""
+    word = torch.zeros(1, device="cuda")
+    for _ in range(8):
+        s = RestoreSession(gc.ctx)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s.compute_stream):
+            torch.cuda._sleep(20_000_000)
+        with torch.cuda.stream(s.copy_stream):
+            word.fill_(1)
+        s.copy_stream.synchronize()
+        apart = not s.compute_stream.query()
+        torch.cuda.synchronize()
+        if apart:
+            return s
+    pytest.skip("no two streams on different hardware queues")
+
+
+@pytest.mark.parametrize("budget", [False, True])
+def test_direct_transfers_leave_the_compute_stream_free(budget):
+    """40 chunks of 2.4 MB (97 MB), in windows of 8, installed straight from
+    pinned memory: alone, or beside a second bound request.  Work that the
+    caller queues on the compute stream does not wait for the installs of
+    earlier calls after the first (it is done while the copy stream, and the
+    second window on it, is still held up), and comes before the installs of
+    later calls (it fills their blocks with a pattern, late, and they overwrite
+    it)."""
+    W, C = 8, 64
+    xi, yi = _variant(2, 3, n_tokens=40 * C, chunk_tokens=C), _variant(2, 103, n_tokens=4 * C, chunk_tokens=C)
+    ctx, slot = _ctx([xi, yi], W, budget=2 * W * 2_426_880 if budget else 0)
+    try:
+        assert slot == 2_426_880
+        x, y = Tenant(ctx, xi, 95, W), Tenant(ctx, yi, 96, W)
+        x.sess = _concurrent_session(x)
+        copy, compute = x.sess.copy_stream, x.sess.compute_stream
+        second = int(xi.block_tables[0][W * C // xi.workload.groups[0].block_tokens])  # of chunk W
+        before = x.dev.pools[0][0][second].cpu()
+        late = [torch.from_numpy(t[2 * W * C // s.block_tokens:40 * C // s.block_tokens]).long().cuda()
+                for t, s in zip(xi.block_tables, xi.workload.groups)]
+        say(f"case: 40 chunks of {slot} B, direct, {'beside another request' if budget else 'alone'}")
+        log = []
+        for t in (x, y):
+            t.probe()
+        assert _bind(x, log)
+        if budget:
+            assert _bind(y, log)
+        with torch.cuda.stream(copy):
+            torch.cuda._sleep(200_000_000)     # far longer than the calls below take
+        mark = torch.cuda.Event()
+        assert x.step() and x.step()
+        mark.record(compute)
+        mark.synchronize()
+        now = x.dev.pools[0][0][second].cpu()
+        assert not copy.query() and torch.equal(now, before)
+        copy.synchronize()
+        with torch.cuda.stream(compute):
+            torch.cuda._sleep(200_000_000)
+            for pools, blocks in zip(x.dev.pools, late):
+                for p in pools:
+                    p.index_fill_(0, blocks, 0x5B)
+        while x.step():
+            pass
+        x.commit()
+        x.check_success()
+        assert x.out.stats["n_stage_launches"] == 0
+        if budget:
+            while y.step():
+                pass
+            y.commit()
+            y.check_success()
     finally:
         bsr.bsr_ctx_destroy(ctx)
