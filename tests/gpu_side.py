@@ -29,6 +29,23 @@ def say(*a) -> None:
     sys.stdout.flush()
 
 
+# Both routes of a small pinned request: installed straight from pinned memory
+# (k_install_direct), or staged in the ring (k_stage, k_install, k_verify).
+ROUTES = [0, bsr.BSR_FLAG_TWO_STREAMS]
+
+
+def check_route(ctx, request_id: int, stats: dict, flags: int) -> None:
+    """Every install launch of the (completed) request took the route of
+    ``flags``; its chunks are all in the pinned store."""
+    direct = bsr.bsr_direct_stats(ctx, request_id)
+    if flags & bsr.BSR_FLAG_TWO_STREAMS:
+        assert direct["n_launches"] == 0 and stats["stage_bytes"] == stats["h2d_bytes"]
+        assert (stats["n_stage_launches"] > 0) == (stats["h2d_bytes"] > 0)
+    else:
+        assert stats["n_stage_launches"] == 0 and direct["n_launches"] == stats["n_install_launches"]
+        assert direct["bytes"] == stats["installed_bytes"]
+
+
 class GpuCase:
     """Library context + pinned store holding the workload's chunks + device pools."""
 

@@ -24,7 +24,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_side import layout_of, say
+from gpu_side import ROUTES, layout_of, say
 from oracle_side import build_case
 from paper_2608_17826_amd import bsr
 from paper_2608_17826_amd.session import RestoreSession, group_dsts
@@ -122,10 +122,10 @@ class Tenant:
             np.testing.assert_array_equal(self.pool_host(g)[:, others], self.case.pools[g][:, others])
 
 
-def _ctx(wis, W, budget, max_bound=0):
+def _ctx(wis, W, budget, max_bound=0, flags=0):
     layout = layout_of(wis[0])
     ctx = bsr.bsr_ctx_create(layout, W, hip_device=0, staging_budget_bytes=budget,
-                             max_bound_requests=max_bound)
+                             max_bound_requests=max_bound, flags=flags)
     slot = bsr.bsr_slot_bytes(layout)
     stride = (slot + 4095) // 4096 * 4096
     bsr.bsr_store_reserve(ctx, stride * (sum(wi.workload.held_chunks for wi in wis) + 2))
@@ -178,7 +178,7 @@ def test_two_bound_interleaved_third_waits_for_budget():
         _interleave([b, c])
         b.commit()
         c.commit()
-        # runs staged while another request was bound went to the copy engine
+        # while another request was bound, chunks were installed straight from pinned memory
         assert a.out.stats["n_stage_launches"] == b.out.stats["n_stage_launches"] == 0
         events = [("bind", 10, 32), ("bind", 11, 32), ("bind", 12, 32), ("end", 10), ("bind", 12, 32),
                   ("end", 11), ("end", 12)]
@@ -196,10 +196,11 @@ def test_two_bound_interleaved_third_waits_for_budget():
         bsr.bsr_ctx_destroy(ctx)
 
 
-def test_failure_in_one_request_leaves_the_others_intact():
+@pytest.mark.parametrize("flags", ROUTES)
+def test_failure_in_one_request_leaves_the_others_intact(flags):
     W = 8
     wis = [_variant(2, 2 + 100 * j, n_tokens=8192) for j in range(3)]
-    ctx, slot = _ctx(wis, W, budget=3 * W * 9_707_520)
+    ctx, slot = _ctx(wis, W, budget=3 * W * 9_707_520, flags=flags)
     try:
         corrupt = lambda case, keys: case.store.corrupt(keys[5], 1, 1001, 0x5A)   # noqa: E731
         missing = lambda case, keys: case.store.remove(keys[12], 0)               # noqa: E731
@@ -232,13 +233,15 @@ def test_failure_in_one_request_leaves_the_others_intact():
         bsr.bsr_ctx_destroy(ctx)
 
 
-def test_staging_path_changes_mid_request():
-    """A request staged by the staging kernel while bound alone switches to
-    the copy engine when a second one binds, and back once the second one
-    has committed; both images are the oracle's."""
+@pytest.mark.parametrize("flags", ROUTES)
+def test_staging_path_changes_mid_request(flags):
+    """A request staged by the staging kernel while bound alone is installed
+    straight from pinned memory once a second one binds (staged by the copy
+    engine with BSR_FLAG_TWO_STREAMS), and staged again once the second one has
+    committed; both images are the oracle's."""
     W = 8
     wis = [_variant(2, 2 + 100 * j, n_tokens=8192) for j in range(2)]
-    ctx, slot = _ctx(wis, W, budget=2 * W * 9_707_520)
+    ctx, slot = _ctx(wis, W, budget=2 * W * 9_707_520, flags=flags)
     try:
         x = Tenant(ctx, wis[0], 70, W)
         y = Tenant(ctx, wis[1], 71, W)
@@ -248,7 +251,7 @@ def test_staging_path_changes_mid_request():
         assert _bind(x, log)
         assert x.step() and x.step()          # windows 0-1 of x alone: staging kernel
         assert _bind(y, log)
-        assert x.step() and y.step()          # x's window 2 beside y: copy engine
+        assert x.step() and y.step()          # x's window 2 beside y
         while y.step():
             pass
         y.commit()
@@ -259,6 +262,8 @@ def test_staging_path_changes_mid_request():
         y.check_success()
         runs_x, runs_y = x.out.stats["n_stage_launches"], y.out.stats["n_stage_launches"]
         assert runs_x > 0 and runs_y == 0
+        direct = [bsr.bsr_direct_stats(ctx, t.rid)["n_launches"] for t in (x, y)]
+        assert all(direct) if flags == 0 else not any(direct)
         assert 0 < x.out.stats["stage_bytes"] < x.out.stats["h2d_bytes"]
     finally:
         bsr.bsr_ctx_destroy(ctx)

@@ -12,7 +12,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_side import GpuCase, layout_of, say
+from gpu_side import ROUTES, GpuCase, check_route, layout_of, say
 from oracle_side import build_case
 from paper_2608_17826_amd import bsr
 from workloads import generate, get_config
@@ -85,31 +85,35 @@ def test_keys_and_probe_bit_exact():
         gc.close()
 
 
-def test_config1_full_parity():
-    say("case: workload 1, W=2, full parity")
+@pytest.mark.parametrize("flags", ROUTES)
+def test_config1_full_parity(flags):
+    say(f"case: workload 1, W=2, flags={flags}, full parity")
     wi = generate(get_config(1))
     case, n, _, _, res = _oracle(wi, 2)
-    gc = GpuCase(wi, W=2)
+    gc = GpuCase(wi, W=2, flags=flags)
     try:
         assert gc.probe(1)[0] == n == 16
         out = gc.restore(1, n)
         _compare_success(gc, case, res, out)
+        check_route(gc.ctx, 1, out.stats, flags)
     finally:
         gc.close()
 
 
+@pytest.mark.parametrize("flags", ROUTES)
 @pytest.mark.parametrize("seed", range(10))
-def test_random_layout_parity(seed):
+def test_random_layout_parity(seed, flags):
     w = random_workload(seed)
     wi = generate(w)
     for W in w.windows:
-        say(f"case: random layout seed={seed} W={W} groups={[(s.kind, s.block_tokens, s.record_bytes) for s in w.groups]} C={w.chunk_tokens}")
+        say(f"case: random layout seed={seed} W={W} flags={flags} groups={[(s.kind, s.block_tokens, s.record_bytes) for s in w.groups]} C={w.chunk_tokens}")
         case, n, _, _, res = _oracle(wi, W)
-        gc = GpuCase(wi, W=W)
+        gc = GpuCase(wi, W=W, flags=flags)
         try:
             assert gc.probe(5)[0] == n
             out = gc.restore(5, n)
             _compare_success(gc, case, res, out)
+            check_route(gc.ctx, 5, out.stats, flags)
         finally:
             gc.close()
 
@@ -124,7 +128,7 @@ def test_random_layout_batch_and_flags_parity(seed):
     W = int(rng.choice(w.windows))
     batch = int(rng.integers(1, min(W, bsr.BSR_MAX_INSTALL_BATCH) + 1))
     flags = bsr.BSR_FLAG_TRUSTED_TABLES if rng.random() < 0.5 else 0
-    if rng.random() < 0.5:   # these requests are small: force the two-stream path on half of them
+    if rng.random() < 0.5:   # these requests are small: half of them go through the ring, on two streams
         flags |= bsr.BSR_FLAG_TWO_STREAMS
     say(f"case: random layout seed={seed} W={W} install_batch={batch} flags={flags}")
     case, n, _, _, res = _oracle(wi, W)
@@ -135,6 +139,7 @@ def test_random_layout_batch_and_flags_parity(seed):
         _compare_success(gc, case, res, out)
         assert out.stats["install_batch"] == batch
         assert out.stats["n_install_launches"] == -(-n // batch) if n else True
+        check_route(gc.ctx, 41, out.stats, flags)
     finally:
         gc.close()
 
@@ -158,7 +163,7 @@ def test_config2_full_parity(batch):
 @pytest.mark.parametrize("slow", ["compute", "copy"])
 def test_slot_reuse_gated_by_events_not_timing(workload, W, batch, slow):
     """(Both workloads on two streams: the small one is forced there, since a
-    request that small is otherwise staged on the compute stream.)"""
+    request that small is otherwise installed straight from pinned memory.)"""
     """Slot reuse is ordered by HIP events, not by how fast either stream
     runs.  Before every window a bounded spin kernel is queued on one of the
     session's streams: on the compute stream the installs lag far behind the
@@ -186,10 +191,11 @@ def test_slot_reuse_gated_by_events_not_timing(workload, W, batch, slow):
         gc.close()
 
 
+@pytest.mark.parametrize("flags", ROUTES)
 @pytest.mark.parametrize("mode,k", [("missing", 0), ("missing", 5), ("corrupt", 1), ("corrupt", 15),
                                     ("timeout", 7), ("transfer", 3), ("abort", 2)])
-def test_config1_failure_parity(mode, k):
-    say(f"case: workload 1 failure {mode} at {k}")
+def test_config1_failure_parity(mode, k, flags):
+    say(f"case: workload 1 failure {mode} at {k}, flags={flags}")
     wi = generate(get_config(1))
     kw = {}
     gkw = {}
@@ -206,7 +212,7 @@ def test_config1_failure_parity(mode, k):
     if mode == "abort":
         kw["abort_after_windows"] = k
     case, n, _, okeys, res = _oracle(wi, 2, mutate=mut, **kw)
-    gc = GpuCase(wi, W=2, timeout_ms=50 if mode == "timeout" else 0)
+    gc = GpuCase(wi, W=2, flags=flags, timeout_ms=50 if mode == "timeout" else 0)
     try:
         n_g, _, keys = gc.probe(3)
         if mode == "missing":
@@ -219,6 +225,7 @@ def test_config1_failure_parity(mode, k):
             bsr.bsr_debug_inject(gc.ctx, bsr.BSR_INJECT_TRANSFER_ERROR, k, 0)
         out = gc.restore(3, n_g, abort_after_windows=kw.get("abort_after_windows"))
         _compare_failure(gc, case, res, out)
+        check_route(gc.ctx, 3, out.stats, flags)
         # force-local: the next admission sees no external tokens until RUNNING/teardown
         assert gc.probe(3)[0] == 0
         bsr.bsr_request_running(gc.ctx, 3)
@@ -228,8 +235,9 @@ def test_config1_failure_parity(mode, k):
         gc.close()
 
 
+@pytest.mark.parametrize("flags", ROUTES)
 @pytest.mark.parametrize("seed", range(50))
-def test_random_layout_failure_parity(seed):
+def test_random_layout_failure_parity(seed, flags):
     """Random layouts x a seeded fault (missing / corrupt entry in a random
     group, timeout, transfer error, abort) at a seeded chunk."""
     w = random_workload(seed)
@@ -251,7 +259,7 @@ def test_random_layout_failure_parity(seed):
     byte = int(rng.integers(0, layout.payload_bytes(g)))
     mask = int(rng.integers(1, 256))
     abort_k = int(rng.integers(1, n_windows)) if mode == "abort" else None
-    say(f"case: random layout seed={seed} W={W} fault {mode} chunk {k} group {g}")
+    say(f"case: random layout seed={seed} W={W} fault {mode} chunk {k} group {g} flags={flags}")
     kw = {}
     if mode == "missing":
         mut = lambda case, keys: case.store.remove(keys[k], g)  # noqa: E731
@@ -265,7 +273,7 @@ def test_random_layout_failure_parity(seed):
         kw["abort_after_windows"] = abort_k
     case, n, _, _, res = _oracle(wi, W, mutate=mut, **kw)
     assert n == n_full
-    gc = GpuCase(wi, W=W, timeout_ms=50 if mode == "timeout" else 0)
+    gc = GpuCase(wi, W=W, flags=flags, timeout_ms=50 if mode == "timeout" else 0)
     try:
         n_g, _, keys = gc.probe(40)
         assert n_g == n
@@ -279,6 +287,7 @@ def test_random_layout_failure_parity(seed):
             bsr.bsr_debug_inject(gc.ctx, bsr.BSR_INJECT_TRANSFER_ERROR, k, 0)
         out = gc.restore(40, n_g, abort_after_windows=abort_k)
         _compare_failure(gc, case, res, out)
+        check_route(gc.ctx, 40, out.stats, flags)
         assert gc.probe(40)[0] == 0
     finally:
         gc.close()
@@ -405,8 +414,9 @@ def test_corruption_before_a_mark_stays_the_recorded_failure():
 _MARK_SEEDS = [s for s in range(40) if random_workload(s).n_full_chunks >= 2][:12]
 
 
+@pytest.mark.parametrize("flags", ROUTES)
 @pytest.mark.parametrize("seed", _MARK_SEEDS)
-def test_random_layout_group_marked_mid_restore(seed):
+def test_random_layout_group_marked_mid_restore(seed, flags):
     """Random layouts: a seeded group is marked invalid after a seeded window
     (never the last), with a seeded install batch."""
     w = random_workload(seed)
@@ -418,15 +428,16 @@ def test_random_layout_group_marked_mid_restore(seed):
     g = int(rng.integers(0, len(w.groups)))
     batch = int(rng.integers(1, W + 1))
     wi = generate(w)
-    say(f"case: random layout seed={seed} W={W} batch={batch} group {g} marked after window {after} of {n_windows}")
+    say(f"case: random layout seed={seed} W={W} batch={batch} flags={flags} group {g} marked after window {after} of {n_windows}")
     case, n, _, _, res = _oracle(wi, W, invalid_groups=[g])
-    gc = GpuCase(wi, W=W, install_batch=batch)
+    gc = GpuCase(wi, W=W, install_batch=batch, flags=flags)
     try:
         n_g = gc.probe(10)[0]
         assert n_g == n == n_full
         out = gc.restore(10, n_g, after_window=lambda j: j + 1 == after and bsr.bsr_mark_group_invalid(gc.ctx, 10, g))
         assert out.window_errors == []
         _compare_failure(gc, case, res, out)
+        check_route(gc.ctx, 10, out.stats, flags)
     finally:
         gc.close()
 
@@ -447,18 +458,20 @@ def _eight_group_workload():
                     groups=tuple(specs), windows=(32,), pool_factor=2)
 
 
-def test_max_groups_and_max_install_batch():
+@pytest.mark.parametrize("flags", ROUTES)
+def test_max_groups_and_max_install_batch(flags):
     wi = generate(_eight_group_workload())
     assert len(wi.workload.groups) == bsr.BSR_MAX_GROUPS
-    say("case: eight groups, W=32, install batch 32 (both maxima)")
+    say(f"case: eight groups, W=32, install batch 32 (both maxima), flags={flags}")
     case, n, _, _, res = _oracle(wi, 32)
     assert n == 40
-    gc = GpuCase(wi, W=32, install_batch=bsr.BSR_MAX_INSTALL_BATCH)
+    gc = GpuCase(wi, W=32, install_batch=bsr.BSR_MAX_INSTALL_BATCH, flags=flags)
     try:
         assert gc.probe(12)[0] == n
         out = gc.restore(12, n)
         _compare_success(gc, case, res, out)
         assert out.stats["install_batch"] == 32 and out.stats["n_install_launches"] == 2
+        check_route(gc.ctx, 12, out.stats, flags)
     finally:
         gc.close()
 
@@ -481,7 +494,8 @@ def _serpentine_workload():
 def test_serpentine_launches_full_parity():
     """Launches of 28 (the default batch) or 32 chunks take the serpentine
     order, the last, ragged launch (12 or 8 chunks) does not; the whole image
-    is the oracle's either way."""
+    is the oracle's either way.  (Staged in the ring: a request of this size is
+    otherwise installed straight from pinned memory, in plain order.)"""
     wi = generate(_serpentine_workload())
     slot = bsr.bsr_slot_bytes(layout_of(wi))
     assert 28 * slot > (256 << 20) and 12 * slot <= (256 << 20)
@@ -489,12 +503,14 @@ def test_serpentine_launches_full_parity():
     assert n == 40
     for rid, batch in ((14, 0), (15, 32)):
         say(f"case: five groups, {slot} B chunks, W=32, install batch {batch or 28}, serpentine launches")
-        gc = GpuCase(wi, W=32, install_batch=batch)
+        flags = bsr.BSR_FLAG_TWO_STREAMS
+        gc = GpuCase(wi, W=32, install_batch=batch, flags=flags)
         try:
             assert gc.probe(rid)[0] == n
             out = gc.restore(rid, n)
             _compare_success(gc, case, res, out)
-            assert out.stats["n_install_launches"] == 2
+            assert out.stats["install_batch"] == (batch or 28) and out.stats["n_install_launches"] == 2
+            check_route(gc.ctx, rid, out.stats, flags)
         finally:
             gc.close()
 
@@ -519,30 +535,33 @@ def test_copy_runs_follow_the_arena_layout():
         gc.close()
 
 
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("seed", [0, 4, 9])
-def test_trusted_tables_parity(seed):
+def test_trusted_tables_parity(seed, route):
     """BSR_FLAG_TRUSTED_TABLES: no block-table readback at bind; same image."""
     w = random_workload(seed)
     wi = generate(w)
     W = w.windows[1]
     say(f"case: trusted tables, random layout seed={seed} W={W}")
     case, n, _, _, res = _oracle(wi, W)
-    gc = GpuCase(wi, W=W, flags=bsr.BSR_FLAG_TRUSTED_TABLES)
+    gc = GpuCase(wi, W=W, flags=bsr.BSR_FLAG_TRUSTED_TABLES | route)
     try:
         assert gc.probe(31)[0] == n
         out = gc.restore(31, n)
         _compare_success(gc, case, res, out)
+        check_route(gc.ctx, 31, out.stats, route)
     finally:
         gc.close()
 
 
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("bad", ["past_pool", "negative"])
-def test_trusted_tables_bad_id_fails_closed(bad):
+def test_trusted_tables_bad_id_fails_closed(bad, route):
     """An advertised id outside its pool, unchecked at bind, fails the request
     on the device: nothing is written, nothing is exposed (Prop. 2)."""
     wi = generate(get_config(1))
     say(f"case: trusted tables, workload 1, block_table[37] {bad}")
-    gc = GpuCase(wi, W=2, flags=bsr.BSR_FLAG_TRUSTED_TABLES)
+    gc = GpuCase(wi, W=2, flags=bsr.BSR_FLAG_TRUSTED_TABLES | route)
     try:
         pb = wi.pool_blocks[0]
         gc.dev.block_tables[0][37] = pb if bad == "past_pool" else -5
@@ -550,6 +569,7 @@ def test_trusted_tables_bad_id_fails_closed(bad):
         n = gc.probe(32)[0]
         out = gc.restore(32, n)
         assert out.exposed_tokens == 0 and out.fallback == 1
+        check_route(gc.ctx, 32, out.stats, route)
         assert out.status["fail"] == bsr.BSR_FAIL_BLOCK_TABLE
         assert out.status["first_failed_chunk"] == 37 * 16 // 64
         assert out.status["q"][0] == 0
@@ -661,16 +681,20 @@ def test_xcd_work_order_spans_and_ragged_tail(batch, grid):
     piece per (tensor, chunk) gives 36 work items per chunk, so these batch
     sizes make launches below one span, of exactly one span, and of one or
     two spans plus a ragged tail (a span is 36 x the XCD count, 288 on
-    eight XCDs); every image must still equal the oracle's."""
+    eight XCDs); every image must still equal the oracle's.  (Staged in the
+    ring: the kernel that installs straight from pinned memory has a small grid
+    of its own.)"""
     wi = generate(XCD_SPAN_LAYOUT)
     assert 36 * batch == grid
     say(f"case: XCD spans, install batch {batch} (grid {grid})")
     case, n, _, _, res = _oracle(wi, 32)
-    gc = GpuCase(wi, W=32, install_batch=batch)
+    flags = bsr.BSR_FLAG_TWO_STREAMS
+    gc = GpuCase(wi, W=32, install_batch=batch, flags=flags)
     try:
         assert gc.probe(61)[0] == n == 34
         out = gc.restore(61, n)
         _compare_success(gc, case, res, out)
         assert out.stats["n_install_launches"] == -(-n // batch)
+        check_route(gc.ctx, 61, out.stats, flags)
     finally:
         gc.close()

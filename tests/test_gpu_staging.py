@@ -11,7 +11,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_side import GpuCase, layout_of, say
+from gpu_side import ROUTES, GpuCase, check_route, layout_of, say
 from oracle_side import build_case
 from paper_2608_17826_amd import bsr
 from paper_2608_17826_amd.session import RestoreSession, group_dsts
@@ -179,12 +179,15 @@ def test_timing_flags_are_taken_at_bind():
 # (record bytes, chunk tokens): slots of 256 B, one tile (4,096 B), a tile and
 # one 256 B part, and three tiles and a part, none adjacent in the arena but
 # the second
-@pytest.mark.parametrize("flags", [0, bsr.BSR_FLAG_TWO_STREAMS])
+@pytest.mark.parametrize("flags", ROUTES)
 @pytest.mark.parametrize("record,C,W", [(4, 8, 3), (128, 32, 8), (124, 35, 40), (1152, 11, 33)])
 def test_runs_of_a_scattered_store(record, C, W, flags):
-    """Chunks stored one by one in a random order, so that a staging launch
-    takes many runs (up to 32, in one window of more) and runs of one to a
-    few chunks; the image is the oracle's."""
+    """Chunks stored one by one in a random order.  Through the ring, a staging
+    launch takes many runs (up to 32, in one window of more) of one to a few
+    chunks each, so there are fewer launches than chunks: one per batch, one
+    for the rest of a window, and one more where the slots of a batch are
+    released by two earlier ones.  Straight from pinned memory, a launch reads
+    chunks from all over the arena.  The image is the oracle's either way."""
     w = Workload(index=400 + record, name="runs", n_tokens=70 * C + 3, chunk_tokens=C,
                  groups=(GroupSpec("g", 8, 1, record, value_kind="bytes"),), windows=(W,), pool_factor=2)
     wi = generate(w)
@@ -195,7 +198,11 @@ def test_runs_of_a_scattered_store(record, C, W, flags):
         for i in np.random.default_rng(record).permutation(70):
             bsr.bsr_store_put_chunk(gc.ctx, int(gc.keys[i]), wi.payloads(int(i)))
         assert gc.probe(5)[0] == n == 70
-        _check(wi, case, res, gc.restore(5, n), gc.dev.pools, gc.dev.valid)
+        out = gc.restore(5, n)
+        _check(wi, case, res, out, gc.dev.pools, gc.dev.valid)
+        check_route(gc.ctx, 5, out.stats, flags)
+        batches = -(-70 // out.stats["install_batch"])
+        assert out.stats["n_stage_launches"] <= min(69, 2 * batches + out.stats["n_windows"])
     finally:
         gc.close()
 
@@ -313,6 +320,63 @@ def test_requests_beyond_64_mib(tmp_path, n_chunks, in_file, staged):
         out = gc.restore(8, n)
         _check(wi, case, res, out, gc.dev.pools, gc.dev.valid)
         assert out.stats["file_tier_chunks"] == in_file and out.stats["stage_bytes"] == staged << 20
+    finally:
+        gc.close()
+
+
+@pytest.mark.parametrize("n_chunks", [12, 70])
+@pytest.mark.parametrize("fault", ["corrupt", "marked", "aborted", "launch"])
+def test_direct_requests_fail_closed(n_chunks, fault):
+    """Chunks of 1 MiB, installed straight from pinned memory: 12 on the
+    compute stream, 70 by launches on the copy stream.  A corrupt entry in the
+    last chunk, a group marked invalid or the request aborted after its second
+    window, or a failed launch (forced from the host; the chunks it kept are
+    installed before the commit's invalidation): the outcome is the oracle's,
+    and the same context restores the request afterwards."""
+    W = 4 if n_chunks < 64 else 16
+    w = _direct_workload([(64, 3, 1024, 0), (64, 1, 1024, 0)], 256, n_chunks, W)
+    wi = generate(w)
+    case = build_case(wi)
+    n, _, keys = oracle.probe(case.store, wi.tokens, 256, wi.salt)
+    kw = {}
+    if fault == "corrupt":
+        case.store.corrupt(keys[n - 1], 1, 4097, 0x42)
+    elif fault == "marked":
+        kw["invalid_groups"] = [1]
+    elif fault == "aborted":
+        kw["abort_after_windows"] = 2
+    else:
+        kw["faults"] = {W: oracle.FAIL_TRANSFER}
+    res = oracle.windowed_restore(case.layout, case.store, keys, n, W, wi.block_tables, case.pools, case.valid, **kw)
+    say(f"case: direct installs of {n_chunks} chunks of 1 MiB, W={W}, {fault}")
+    gc = GpuCase(wi, W=W)
+    try:
+        assert gc.probe(8)[0] == n == n_chunks
+        if fault == "corrupt":
+            gc.corrupt(int(keys[n - 1]), 1, 4097, 0x42)
+        if fault == "launch":
+            bsr.bsr_debug_inject(gc.ctx, bsr.BSR_INJECT_LAUNCH_ERROR, W, 0)
+
+        def mark(j):
+            if fault == "marked" and j == 1:
+                bsr.bsr_mark_group_invalid(gc.ctx, 8, 1)
+        out = gc.restore(8, n, after_window=mark, abort_after_windows=kw.get("abort_after_windows"))
+        assert out.exposed_tokens == res.exposed_tokens == 0 and out.fallback == 1
+        if fault == "launch":
+            assert [c for _, c in out.window_errors] == [bsr.BSR_E_TRANSFER]
+            assert out.status["fail"] == bsr.BSR_FAIL_TRANSFER
+        else:
+            assert out.status["first_failed_chunk"] == res.first_failed_chunk and out.status["q"][:2] == res.q
+        for g in range(2):
+            np.testing.assert_array_equal(gc.valid_host(g), case.valid[g])
+        check_route(gc.ctx, 8, out.stats, 0)
+        assert gc.probe(8)[0] == 0          # force-local after the fallback
+        bsr.bsr_request_end(gc.ctx, 8)
+        if fault == "corrupt":
+            gc.corrupt(int(keys[n - 1]), 1, 4097, 0x42)
+        case, n, res = _oracle(wi, W)
+        assert gc.probe(9)[0] == n
+        _check(wi, case, res, gc.restore(9, n), gc.dev.pools, gc.dev.valid)
     finally:
         gc.close()
 
