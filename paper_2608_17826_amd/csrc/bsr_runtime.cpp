@@ -71,32 +71,34 @@ constexpr uint64_t kAlign = 256;
 constexpr uint64_t kOneStreamBytes = 64ull << 20;
 // Requests of at most this many chunk bytes, all of them in the pinned store,
 // are installed straight from there when no other request can be bound beside
-// them (no staging budget): the link is loaded from
-// the first chunk to the last, where the ring's pipeline has its first copy and
-// its last install to itself, hands over between two streams at every batch and
-// loses link rate to the installs beside its copies.  Measured in turn, ring
-// and direct: 75 MB of 2.4 MB chunks at W = 8 1,516 and 1,396 us, 155 MB of
-// 607 KB chunks 2,992 and 2,856, 525 MB of 16.4 MB chunks 9,365 and 9,268,
-// 621 MB of 9.7 MB chunks 11,174 and 11,069, 3.15 GB 55.56 and 55.42 ms: the
-// gain, about 100 us a request, is 1% at this line and less beyond, where a
-// staging copy also keeps to 24 CUs for the seconds that it may take.
+// them (no staging budget): the link is loaded from the first chunk to the
+// last, where the ring's pipeline has its first copy and its last install to
+// itself, hands over between two streams at every batch and loses link rate to
+// the installs beside its copies.  Measured in turn, ring and direct: 75 MB of
+// 2.4 MB chunks at W = 8 1,488 and 1,389 us, 155 MB of 607 KB chunks 2,998 and
+// 2,845, 525 MB of 16.4 MB chunks 9,310 and 9,208, 621 MB of 9.7 MB chunks
+// 11,120 and 10,968, 1.24 GB 21.91 and 21.73 ms, 3.15 GB 55.34 and 54.95 ms: the
+// gain is 1% at this line and less beyond, where a staging copy also keeps to
+// 24 CUs for the seconds that it may take.
 constexpr uint64_t kDirectBytes = 768ull << 20;
 // Chunks that the install reads straight from pinned memory are launched at
 // the end of a window once they hold this many bytes, or else join the next
-// window's: a launch costs about 15 us beside its 18 us/MiB of link time.  The
-// 1K-token workload (295 KB windows) takes 132 us with a launch per window,
-// 111 with 512 KiB, 96 with 1 MiB and 99 in one launch, which starts late.
+// window's: a launch costs about 15 us beside its 18 us/MiB of link time, and a
+// later one starts late.  In us per request, from 256 KiB / 512 KiB / 1 MiB /
+// 2 MiB on: 1,024 tokens of one group (2.4 MB in 295 KB windows) 103 / 100 / 96 /
+// 100; 500 tokens of eight groups (1.3 MB in 174 KB windows) 112 / 101 / 94 / 86;
+// 2,000 tokens of one group (4.1 MB in 1.2 MB windows) 131 / 131 / 131 / 129;
+// requests of one window, and 22 MB in 1.2 MB windows, the same.
 constexpr uint64_t kDirectFlushBytes = 1ull << 20;
 // While the launch before is still running, chunks that hold less than the
 // request has launched so far wait for the next window too, up to this many
 // bytes: the launches of many small windows double in size, each about as long
 // as the device still has work before it.  A window that ends with that launch
-// done is launched whatever it holds (from kDirectFlushBytes on), so a caller
-// that pauses between windows leaves the link idle for the part of its pause
-// that the device outlasts, with at most 1.2 ms of link time waiting.
-// Measured in turn, a launch per window and so: 155 MB in
-// 1.2 MB windows 3,735 and 2,882 us, 295 MB in 4.9 MB windows 6,018 and 5,474,
-// 55 MB in 707 KB windows 1,710 and 1,579, 513 MB in 131 MB windows the same.
+// done is launched from kDirectFlushBytes on, so a caller that pauses between
+// windows has 18 us of link time waiting, or what it added while the device was
+// busy, at most 1.2 ms.  Measured in turn, a launch per window and so: 155 MB in 1.2 MB windows 3,516
+// and 2,855 us, 295 MB in 4.9 MB windows 5,983 and 5,422, 55 MB in 707 KB windows
+// 1,311 and 1,210, 509 MB in 131 MB windows the same.
 constexpr uint64_t kDirectHoldBytes = 64ull << 20;
 // Install launches whose staged chunks exceed this many bytes walk their
 // chunks in alternate directions from one dispatch position to the next
@@ -1784,9 +1786,10 @@ int bsr_restore_window(bsr_ctx* c, uint64_t request_id, uint32_t first_chunk, ui
   const uint32_t all_mask = (G >= 32) ? 0xFFFFFFFFu : ((1u << G) - 1);
   const uint32_t E = static_cast<uint32_t>(res.free_ev.size());
   // The install batch may span windows.  A copy into slot i mod W needs the
-  // install of chunk i - W, which is never in the pending batch (it holds at
-  // most install_batch - 1 <= W - 1 earlier chunks), so its release event has
-  // been recorded already.
+  // install of chunk i - W, which is never in the pending batch of staged
+  // chunks (it holds at most install_batch - 1 <= W - 1 earlier ones), so its
+  // release event has been recorded already.  Chunks pending for a direct
+  // launch use no slot, and are launched before any is staged.
   std::vector<uint32_t>& batch = s.pend;
   const uint64_t t_window = now_ns();
   int rc = BSR_OK;
