@@ -511,9 +511,10 @@ int bsr_mark_group_invalid(bsr_ctx* ctx, uint64_t request_id, uint32_t group);
  * Q = (fail == 0) and q_g for every group.  Q = 1: exposed = n*chunk_tokens
  * and every advertised block's valid byte = 1.  Q = 0: exposed = 0, every
  * advertised block in every group invalid, fallback = 1, and the request's
- * force-local marker is set.  Then waits for the compute stream, reads the
- * status back, releases store references and the request's admission (the
- * lock, or its share of B).
+ * force-local marker is set.  Then waits for the compute stream (and for the
+ * copy stream, if installs ran there: the commit kernel is behind them),
+ * reads the status back, releases store references and the request's
+ * admission (the lock, or its share of B).
  * Returns BSR_OK in both cases; exposed_tokens / fallback (either may be
  * NULL) report which.  All windows need not have been restored: a commit
  * before the last window exposes nothing (the prefix is incomplete). */

@@ -446,3 +446,32 @@ def test_direct_chunks_wait_only_while_the_device_is_busy(batch, paused):
         assert launches == ([1, 2, 3, 4, 5, 6] if paused else [1, 2, 2, 3, 3, 4])
     finally:
         gc.close()
+
+
+@pytest.mark.parametrize("n_chunks", [12, 70])
+def test_direct_installs_under_capture(n_chunks):
+    """The windows of a bound request captured into a graph from the compute
+    stream (chunks of 1 MiB: 12 on that stream alone, 70 with launches on the
+    copy stream, joined again when the prefix is complete).  Nothing is
+    installed until the graph is launched; then the commit exposes the
+    oracle's image."""
+    w = _direct_workload([(64, 4, 1024, 0)], 256, n_chunks, 16)
+    wi = generate(w)
+    case, n, res = _oracle(wi, 16)
+    say(f"case: {n_chunks} chunks of 1 MiB, W=16, windows captured")
+    gc = GpuCase(wi, W=16)
+    try:
+        assert gc.probe(8)[0] == n == n_chunks
+        sess, graph = gc.session, torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        sess.bind(8, n, gc.dsts())
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=sess.compute_stream, capture_error_mode="thread_local"):
+            for first, cnt in sess.next_windows(8):
+                bsr.bsr_restore_window(gc.ctx, 8, first, cnt)
+        np.testing.assert_array_equal(gc.pool_host(0), wi.sentinel_pool(0))
+        with torch.cuda.stream(sess.compute_stream):
+            graph.replay()
+        _check(wi, case, res, sess.commit(8), gc.dev.pools, gc.dev.valid)
+    finally:
+        gc.close()
